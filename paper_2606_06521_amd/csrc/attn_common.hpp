@@ -46,6 +46,7 @@ struct Params {
     int Nk;              // cached keys per (batch, kv head); N for self-attention
     int qoff;            // Nk - N: query row r sits at key position r + qoff
     int order;           // 0 forward, 1 reverse
+    int causal;          // faithful kernel (the fast kernels take it as a template argument)
     int n_sink;
     float S;             // static P-scale (2^k0 with the dynamic scale)
     float inv_S;         // 1/S, used only when S is a power of two (exact)
@@ -177,6 +178,31 @@ __device__ inline float halves_sum(float x)
 }
 
 __device__ inline float fmax_f(float a, float b) { return __builtin_fmaxf(a, b); }
+
+// exp2 in FP64, rounded once to FP32, for x <= 0 or barely above (any x below
+// 128 is right): 2^n times the degree-11 Chebyshev interpolant of 2^f on
+// [-1/2, 1/2] (relative error 2^-55), f = x - n exact.  x = -inf gives 0, NaN
+// stays NaN.  The library's exp2 costs seven instructions more per value
+// (range checks and selects).
+__device__ inline float exp2_f64(float x)
+{
+    const float xc = __builtin_elementwise_maximum(x, -160.f);   // 2^-160 rounds to 0
+    const float n = __builtin_rintf(xc);
+    const double f = (double)(xc - n);
+    double q = 0x1.e9ec1fcb69a7fp-32;
+    q = __builtin_fma(q, f, 0x1.e6228acd1c6e5p-28);
+    q = __builtin_fma(q, f, 0x1.b524ebd13a55fp-24);
+    q = __builtin_fma(q, f, 0x1.62bfc2c86d700p-20);
+    q = __builtin_fma(q, f, 0x1.ffcbfc6da6ed1p-17);
+    q = __builtin_fma(q, f, 0x1.430913112c61bp-13);
+    q = __builtin_fma(q, f, 0x1.5d87fe78a3f9cp-10);
+    q = __builtin_fma(q, f, 0x1.3b2ab6fb9f1a5p-7);
+    q = __builtin_fma(q, f, 0x1.c6b08d704a0c6p-5);
+    q = __builtin_fma(q, f, 0x1.ebfbdff82c5aep-3);
+    q = __builtin_fma(q, f, 0x1.62e42fefa39efp-1);
+    q = __builtin_fma(q, f, 1.0);
+    return (float)__builtin_amdgcn_ldexp(q, (int)n);
+}
 
 // Number of zero bytes in a word of four E4M3 codes of non-negative values
 // (every byte <= 0x7F): adding 0x7F to the low seven bits of a byte sets its

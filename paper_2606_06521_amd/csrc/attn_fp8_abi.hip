@@ -289,7 +289,7 @@ int launch(Call& cl, const void* q, const void* k, const void* v, float* out, fl
                 : (pair ? go(attn::launch_fast_t<false, true>) : go(attn::launch_fast_t<false, false>));
     } else {
         e = attn::launch_faithful(p, cl.d, cl.block_kv, cl.causal, cl.count,
-                                  cl.mode == ATTN_MODE_FAITHFUL, cl.dyn, s);
+                                  cl.mode == ATTN_MODE_FAITHFUL, scale, n_cu, s);
     }
     return e == hipSuccess ? ATTN_OK : ATTN_ERR_HIP;
 }
@@ -335,7 +335,7 @@ int run(const void* q, const void* k, const void* v, float* out, float* lse,
     if (st != ATTN_OK)
         return st;
     int n_cu = 0;
-    if (cl.fast && (st = device_cus(n_cu)) != ATTN_OK)
+    if ((st = device_cus(n_cu)) != ATTN_OK)
         return st;
     if (ws && ws_bytes < workspace_bytes(cl, n_cu))
         return ATTN_ERR_INVALID_ARG;
@@ -439,7 +439,7 @@ int attn_fp8_fwd_kv_noalloc(const void* q, const void* k, const void* v, float* 
     if (st != ATTN_OK)
         return st;
     int n_cu = 0;
-    if (cl.fast && (st = device_cus(n_cu)) != ATTN_OK)
+    if ((st = device_cus(n_cu)) != ATTN_OK)
         return st;
     const size_t need = workspace_bytes(cl, n_cu);
     if (need > kScratchBytes)

@@ -6,8 +6,9 @@
 
 namespace attn {
 
+// sets its own tile geometry and grid in p
 hipError_t launch_faithful(const Params& p, int d, int block_kv, bool causal, bool count,
-                           bool cast, bool dynamic, hipStream_t stream);
+                           bool cast, int scale, int n_cu, hipStream_t stream);
 int faithful_rows_per_wg();
 
 // The fast kernel (persistent): QK8 selects E4M3 Q and K (S^T on the FP8

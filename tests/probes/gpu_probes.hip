@@ -18,15 +18,18 @@
 //     two waves of a SIMD (the fast kernel's ping-pong) or interleaved in one
 //     wave per SIMD, and what each MFMA shape costs the vector wave.
 // Every kernel bounds-checks its index against n.
-#include <hip/hip_runtime.h>
-#include <stdint.h>
+#include "../../paper_2606_06521_amd/csrc/attn_common.hpp"
 
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
-typedef __attribute__((__vector_size__(8 * sizeof(int)))) int i32x8;
+using namespace attn;
 typedef __attribute__((__vector_size__(2 * sizeof(short)))) short s16x2;
-typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4;
-typedef __attribute__((__vector_size__(2 * sizeof(int)))) int i32x2;
+
+// the FP32 modes' exp2 (FP64, rounded once)
+__global__ void k_exp2_f64(const float* x, int64_t n, float* out)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n)
+        out[i] = exp2_f64(x[i]);
+}
 
 __global__ void k_cvt_range(uint32_t lo, int64_t n, uint8_t* out)
 {
@@ -496,6 +499,14 @@ int probe_cvt_list(const float* x, int64_t n, uint8_t* out, float scale, int sca
         return -1;
     hipLaunchKernelGGL(k_cvt_list, dim3(grid_for((n + 1) / 2, 256)), dim3(256), 0,
                        (hipStream_t)stream, x, n, out, scale, scaled, hi);
+    return hipGetLastError() == hipSuccess ? 0 : -3;
+}
+
+int probe_exp2_f64(const float* x, int64_t n, float* out, void* stream)
+{
+    if (n <= 0 || !x || !out)
+        return -1;
+    hipLaunchKernelGGL(k_exp2_f64, dim3(grid_for(n, 256)), dim3(256), 0, (hipStream_t)stream, x, n, out);
     return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 

@@ -1,0 +1,58 @@
+"""The FP32 kernel's tile and workgroup shapes (16- or 32-row tiles, four or
+eight waves, one or two workgroups per tile), chosen by how far the tiles fill
+the chip, each at lengths that leave partial tiles, partial last blocks and
+rounds with idle waves, against the oracle on every row; and its exp2."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2606_06521_amd.inputs import last_queries, make_inputs
+from tests.gpu_helpers import compare, log, run_gpu, to_device
+
+pytestmark = pytest.mark.gpu
+
+# (heads, query rows, keys): with 256 compute units, 32-row tiles on four waves
+# (512 tiles or more), on eight (256 or more), 16-row tiles (more than 128), and two
+# workgroups per 16-row tile
+SHAPES = [(172, 65, 65), (104, 79, 129), (40, 50, 50), (33, 49, 700), (3, 17, 1025), (1, 1, 130)]
+
+
+@pytest.mark.parametrize("d,block_kv", [(64, 64), (128, 128), (128, 64), (64, 128)])
+@pytest.mark.parametrize("H,nq,nk", SHAPES)
+def test_shapes_against_oracle(H, nq, nk, d, block_kv):
+    inp = make_inputs(1, H, H, nk, d, fmt="f32", delta=8.0, seed=1700 + H)
+    if nq < nk:
+        inp = last_queries(inp, nq)
+    dev = to_device(inp)
+    for i, (mode, S, order, causal, scale) in enumerate([
+            ("faithful", 256.0, "reverse", True, "static"), ("faithful", 3.0, "forward", False, "static"),
+            ("faithful", 16.0, "forward", True, "dynamic"), ("nocast", 448.0, "reverse", False, "static")]):
+        label = f"faithful shape H={H} nq={nq} nk={nk} d={d} bk={block_kv} #{i}"
+        log(label)
+        gpu = run_gpu(dev, mode, S, order, causal, block_kv, scale=scale)
+        compare(inp, gpu, mode, S, order, causal, block_kv, label=label, scale=scale)
+
+
+def test_exp2_is_correctly_rounded():
+    # against FP64 exp2 rounded once: equal, but for values whose FP64 result lies
+    # within its own error (2^-51 relative, both sides) of a rounding midpoint:
+    # one value in 2^27, so at most a handful of 2^22
+    from tests import probes as pr
+    rng = np.random.default_rng(3)
+    edge = np.arange(-160, 1).astype(np.float32)
+    x = np.concatenate([edge, np.nextafter(edge, np.float32(-np.inf)), np.nextafter(edge, np.float32(1)),
+                        edge + np.float32(0.5), np.float32([-np.inf, -1e30, -0.0]),
+                        rng.uniform(-40, 0, 1 << 21).astype(np.float32),
+                        (-np.exp2(rng.uniform(-30, 8, 1 << 21))).astype(np.float32)])
+    xt = torch.from_numpy(x).cuda()
+    out = torch.empty_like(xt)
+    assert pr.lib().probe_exp2_f64(xt.data_ptr(), x.size, out.data_ptr(),
+                                   torch.cuda.current_stream().cuda_stream) == 0
+    got = out.cpu().numpy()
+    want = np.exp2(x.astype(np.float64)).astype(np.float32)
+    bad = np.nonzero(got != want)[0]
+    assert bad.size <= 4, [(float(x[i]), float(got[i]), float(want[i])) for i in bad[:8]]
+    nan = torch.full((64,), float("nan"), device="cuda")
+    assert pr.lib().probe_exp2_f64(nan.data_ptr(), 64, nan.data_ptr(),
+                                   torch.cuda.current_stream().cuda_stream) == 0
+    assert torch.isnan(nan).all()
