@@ -218,24 +218,27 @@ int attn_fp8_p_underflow_count_descaled(const void* q, const void* k, const void
  *   counts [B][Hq][Nq][3] (count variant).
  *
  * With Nq = Nk these are attn_fp8_fwd_descaled / _p_underflow_count_descaled.
- * With Nq < Nk the fast modes run on a prefill kernel: the eight waves of a
- * workgroup split a 32-row tile's KV blocks into contiguous ranges of the
- * visit order; each range starts from the running maximum the row reached
- * before it, so the P codes are those of the sequential visit; only the FP32
+ * With Nq < Nk the fast modes run on a KV-cache kernel: the query rows of the
+ * heads that share a KV head form tiles of 16 or 32 rows, and the eight waves
+ * of a workgroup take a tile's KV blocks in rounds, handing the running
+ * maximum on, so the P codes are those of the sequential visit; only the FP32
  * summation order of O and l differs.  (Long chunks, Nq >= 128 with Nk - Nq a
  * multiple of block_kv, run on the square problem's kernel instead.)  When
  * the tiles are fewer than the GPU's compute units, each tile can be split
- * over C = min(CUs / tiles, blocks / 8, 8) workgroups; the call then enqueues
- * three kernels (the range maxima, Algorithm 1 per range, a merge) and needs
- * a device workspace of attn_fp8_kv_workspace_bytes() bytes:
+ * over C = min(CUs / tiles, blocks / 8, 512 / rows) workgroups by ranges of its
+ * keys; the call then enqueues three kernels (the range maxima, Algorithm 1
+ * per range, a merge) and needs a device workspace:
  *   workspace        device memory of the caller, 256-byte aligned, or NULL.
  *                    The call uses it as scratch on `stream` (no contents are
  *                    read before the call writes them); calls that overlap in
- *                    time must not share one.  NULL runs the tiles unsplit
- *                    (same results, fewer workgroups).
- *   workspace_bytes  its size; with a non-NULL workspace it must be at least
- *                    what attn_fp8_kv_workspace_bytes reports for the same
- *                    shape on the current device, else ATTN_ERR_INVALID_ARG.
+ *                    time must not share one.  NULL runs the tiles without
+ *                    that split (same codes and counts, fewer workgroups).
+ *   workspace_bytes  its size; with a non-NULL workspace it should be what
+ *                    attn_fp8_kv_workspace_bytes reports for the same shape on
+ *                    the current device.  Less lowers C, down to
+ *                    T * K * (32 d + 288) * 4 bytes for T = B Hq ceil(Nq / 32) < CUs
+ *                    and K = min(CUs / T, blocks / 8, 8) > 1; below that
+ *                    ATTN_ERR_INVALID_ARG.
  * Nq > Nk returns ATTN_ERR_INVALID_ARG, Nk > 2^30 ATTN_ERR_UNSUPPORTED; other
  * arguments and return codes as
  * for the descaled entry points.
@@ -277,9 +280,10 @@ int attn_fp8_fwd_kv_noalloc(const void* q, const void* k, const void* v, float* 
  * Workspace the KV-cache entry points can use for the shape (B, Hq, Hkv, Nq,
  * Nk, d, causal, block_kv, mode) on the current device: *bytes is set to 0
  * when the call would not split (square problems, long chunks, faithful
- * modes, tiles enough to fill the GPU), else to the size of the range maxima
- * (tiles * C * 8 * 32 floats) plus, from a 256-byte boundary, the partial
- * sums (tiles * C * (32 d + 32) floats).  Since tiles * C never exceeds the
+ * modes, tiles enough to fill the GPU), else to the larger of the range maxima
+ * (units * C * rows floats) plus, from a 256-byte boundary, the partial sums
+ * (units * C * (rows d + rows) floats) of the call's plan, and the least size
+ * above.  Since units * C never exceeds the
  * CU count, this stays below CUs * (32 d + 288) * 4 + 512 bytes (4.5 MB on a
  * 256-CU MI355X at d = 128).  Queries the device's CU count; launches nothing.
  * Returns ATTN_OK, ATTN_ERR_INVALID_ARG (bad shape, NULL bytes),

@@ -161,7 +161,15 @@ int device_cus(int& n_cu)
 // Workspace bytes a prepared call can use (the KV-cache split), on n_cu CUs.
 size_t workspace_bytes(const Call& cl, int n_cu)
 {
-    return cl.prefill ? attn::prefill_workspace_bytes(cl.p, cl.d, cl.block_kv, cl.causal, n_cu) : 0;
+    return cl.prefill ? attn::prefill_workspace_bytes(cl.p, cl.d, cl.block_kv, cl.causal,
+                                                      cl.mode == ATTN_MODE_FP8QK, n_cu)
+                      : 0;
+}
+
+// The least a caller's workspace has to hold (fewer ranges per tile then).
+size_t workspace_min(const Call& cl, int n_cu)
+{
+    return cl.prefill ? attn::prefill_workspace_min(cl.p, cl.d, cl.block_kv, cl.causal, n_cu) : 0;
 }
 
 // Validation of the pointers of a prepared, non-empty call.
@@ -337,7 +345,7 @@ int run(const void* q, const void* k, const void* v, float* out, float* lse,
     int n_cu = 0;
     if ((st = device_cus(n_cu)) != ATTN_OK)
         return st;
-    if (ws && ws_bytes < workspace_bytes(cl, n_cu))
+    if (ws && ws_bytes < workspace_min(cl, n_cu))
         return ATTN_ERR_INVALID_ARG;
     return launch(cl, q, k, v, out, lse, counts, gap_hist, blk_zero, nbins, ws, ws_bytes, n_cu,
                   static_cast<hipStream_t>(stream));
@@ -441,7 +449,7 @@ int attn_fp8_fwd_kv_noalloc(const void* q, const void* k, const void* v, float* 
     int n_cu = 0;
     if ((st = device_cus(n_cu)) != ATTN_OK)
         return st;
-    const size_t need = workspace_bytes(cl, n_cu);
+    const size_t need = workspace_min(cl, n_cu);
     if (need > kScratchBytes)
         return ATTN_ERR_SCRATCH;
     void* ws = nullptr;

@@ -1,0 +1,6 @@
+// KV-cache kernel, E4M3 Q/K, 16-row tiles.
+#include "attn_prefill_kernel.hpp"
+
+namespace attn {
+template hipError_t launch_kv_t<true, 16>(const Params&, int, int, bool, int, int, int, hipStream_t);
+}  // namespace attn

@@ -28,14 +28,26 @@ constexpr int kFastRows = 256;
 constexpr int kFastRowsPair = 128;
 
 // queries against a longer KV cache (p.Nk > p.N), fast modes: one workgroup
-// per (batch, head, 32-row query tile), or several per tile when the tiles
-// cannot fill n_cu compute units and the caller brings a workspace of at least
-// prefill_workspace_bytes() (three launches on the stream); sets its own grid,
-// nsplit and workspace fields of p
+// per (batch, KV head, tile of the group's query rows), or several per tile when
+// the tiles cannot fill n_cu compute units (over the keys only with a
+// workspace: three launches on the stream); sets its own grid, nsplit and
+// workspace fields of p
 hipError_t launch_prefill(const Params& p, int d, int block_kv, bool causal, bool count, int scale,
                           bool qk8, int n_cu, void* ws, size_t ws_bytes, hipStream_t stream);
-// device workspace the split of launch_prefill needs (0: the tiles run unsplit)
-size_t prefill_workspace_bytes(const Params& p, int d, int block_kv, bool causal, int n_cu);
+// One launch of the KV-cache kernel: phase 0 (unsplit), 1 (range maxima) or 2
+// (the visit per range); cols: workgroups per tile that share its columns (phase
+// 0, TR = 16); QK8 selects E4M3 Q and K, TR the tile height.  Each
+// pair is instantiated in its own translation unit.
+template <bool QK8, int TR>
+hipError_t launch_kv_t(const Params& p, int d, int block_kv, bool count, int scale, int phase, int cols,
+                       hipStream_t s);
+extern template hipError_t launch_kv_t<false, 16>(const Params&, int, int, bool, int, int, int, hipStream_t);
+extern template hipError_t launch_kv_t<true, 16>(const Params&, int, int, bool, int, int, int, hipStream_t);
+extern template hipError_t launch_kv_t<false, 32>(const Params&, int, int, bool, int, int, int, hipStream_t);
+extern template hipError_t launch_kv_t<true, 32>(const Params&, int, int, bool, int, int, int, hipStream_t);
+// device workspace launch_prefill can use, and the least it accepts (0: none)
+size_t prefill_workspace_bytes(const Params& p, int d, int block_kv, bool causal, bool qk8, int n_cu);
+size_t prefill_workspace_min(const Params& p, int d, int block_kv, bool causal, int n_cu);
 int prefill_rows_per_wg();
 
 }  // namespace attn

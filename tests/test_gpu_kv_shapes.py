@@ -1,0 +1,68 @@
+"""The KV-cache kernel's plans (16- or 32-row tiles of a group's query rows,
+unsplit, by columns, or over ranges of the keys), each at lengths that leave
+partial tiles, partial last blocks, rounds with idle waves and tiles that hold
+rows of several query heads, against the oracle on every row; and workspaces
+between the least and the reported size."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2606_06521_amd.inputs import last_queries, make_inputs
+from tests.gpu_helpers import compare, log, run_gpu, to_device
+
+pytestmark = pytest.mark.gpu
+
+# (B, Hq, Hkv, Nq, Nk, d, block_kv): the plan on 256 compute units
+SHAPES = [
+    (1, 8, 2, 1, 20000, 128, 128),     # 16 rows, 19 ranges of the keys
+    (1, 8, 8, 3, 515, 64, 64),         # 16 rows, two workgroups by columns
+    (2, 16, 4, 8, 1501, 128, 64),      # the same, rows of two heads per tile
+    (60, 8, 4, 4, 333, 64, 128),       # 16 rows, unsplit
+    (40, 8, 8, 40, 300, 128, 128),     # 32 rows, unsplit
+    (40, 8, 8, 37, 261, 64, 64),       # the same
+    (1, 16, 1, 120, 12001, 128, 128),  # 32 rows, 4 ranges, rows of up to two heads per tile
+]
+
+
+@pytest.mark.parametrize("mode", ["fast", "fp8qk"])
+@pytest.mark.parametrize("B,Hq,Hkv,nq,nk,d,bc", SHAPES)
+def test_plans_against_oracle(B, Hq, Hkv, nq, nk, d, bc, mode):
+    fmt = "e4m3" if mode == "fp8qk" else "bf16_e4m3"
+    inp = last_queries(make_inputs(B, Hq, Hkv, nk, d, fmt=fmt, delta=8.0, seed=2300 + nk), nq)
+    dev = to_device(inp)
+    for S, order, causal, scale in [(256.0, "reverse", True, "static"), (16.0, "forward", False, "dynamic"),
+                                    (3.0, "forward", True, "static")]:
+        label = f"kv plan {mode} B={B} Hq={Hq} Hkv={Hkv} nq={nq} nk={nk} d={d} bc={bc} S={S} {order} {causal}"
+        log(label)
+        gpu = run_gpu(dev, mode, S, order, causal, bc, scale=scale)
+        compare(inp, gpu, mode, S, order, causal, bc, label=label, scale=scale)
+
+
+def test_workspace_sizes():
+    # Reported: room for 32 ranges per tile.  The least a call accepts is what
+    # a split of 32-row tiles per query head over 8 workgroups takes, 64 x (8 x 32 + 32 d + 32)
+    # floats here; anything from there on runs with fewer ranges.
+    from paper_2606_06521_amd import attn_fp8 as A
+    B, Hq, Hkv, nq, nk, d = 1, 8, 8, 1, 40000, 64
+    inp = last_queries(make_inputs(B, Hq, Hkv, nk, d, fmt="bf16_e4m3", delta=8.0, seed=2400), nq)
+    q, k, v = to_device(inp)
+    st, full = A.attn_fp8_kv_workspace_bytes(B, Hq, Hkv, nq, nk, d, 1, 128, A.ATTN_MODE_FAST)
+    least = 4 * 64 * (8 * 32) + 4 * 64 * (32 * d + 32)
+    assert st == 0 and full > least
+    ws = torch.full((full,), 0xFF, dtype=torch.uint8, device="cuda")
+    sptr = torch.cuda.current_stream().cuda_stream
+
+    def call(ptr, nbytes):
+        o = torch.full((B, Hq, nq, d), float("nan"), device="cuda")
+        lse = torch.full((B, Hq, nq), float("nan"), device="cuda")
+        st = A.attn_fp8_fwd_kv(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), lse.data_ptr(), B, Hq,
+                               Hkv, nq, nk, d, 1, 128, 1, 256.0, 1, 1.0, 1.0, 1.0, ptr, nbytes, sptr)
+        torch.cuda.synchronize()
+        return st, o.cpu().numpy(), lse.cpu().numpy()
+
+    for nbytes in (full, (full + least) // 2, least, 0):
+        st, o, lse = call(ws.data_ptr() if nbytes else None, nbytes)
+        assert st == 0
+        log(f"kv workspace {nbytes} of {full}")
+        compare(inp, (o, lse, None), "fast", 256.0, "reverse", True, 128, label=f"workspace {nbytes}")
+    assert call(ws.data_ptr(), least - 1)[0] == A.ATTN_ERR_INVALID_ARG
