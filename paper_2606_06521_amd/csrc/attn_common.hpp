@@ -45,6 +45,7 @@ struct Params {
     int B, Hq, Hkv, N;   // N: query rows per (batch, head)
     int Nk;              // cached keys per (batch, kv head); N for self-attention
     int qoff;            // Nk - N: query row r sits at key position r + qoff
+    int row_lo;          // fast kernel: rows before this one only pad a chunk to a block boundary
     int order;           // 0 forward, 1 reverse
     int causal;          // faithful kernel (the fast kernels take it as a template argument)
     int n_sink;

@@ -105,14 +105,11 @@ int prepare(Call& cl, bool count, int B, int Hq, int Hkv, int N, int Nk, int d, 
     cl.count = count;
     cl.dyn = dyn;
     cl.fast = mode == ATTN_MODE_FAST || mode == ATTN_MODE_FP8QK;
-    // Queries against a longer KV cache (fast modes): long query chunks whose
-    // offset Nk - N is a multiple of the block run on the persistent kernel
-    // (every 32-row wave then still lies in one block of key positions);
-    // short ones, or unaligned offsets, on the prefill kernel, whose waves
-    // share a 32-row tile's KV blocks.
+    // Queries against a longer KV cache (fast modes): short query chunks, and
+    // long ones that start inside a block, may use a workspace (the KV-cache
+    // kernel's split; which kernel runs is decided at the launch).
     cl.prefill = cl.fast && Nk != N && (N < 128 || (Nk - N) % block_kv != 0);
-    // (the fast kernel's tiles are counted at 256 rows here; a launch that
-    // picks the 128-row schedule recounts them)
+    // (the tiles a launch ends up with are counted there)
     const int bm = cl.prefill ? attn::prefill_rows_per_wg()
                               : cl.fast ? attn::kFastRows : attn::faithful_rows_per_wg();
     const int64_t n_tiles = ((int64_t)N + bm - 1) / bm;
@@ -139,11 +136,6 @@ int prepare(Call& cl, bool count, int B, int Hq, int Hkv, int N, int Nk, int d, 
     // stored values, qd and kd the per-tensor descales): c rounded once from double
     p.c = (float)(1.4426950408889634074 * (double)q_descale * (double)k_descale / sqrt((double)d));
     p.v_descale = v_descale;
-    p.n_tiles = (int)n_tiles;
-    p.total_wg = (int)total;
-    p.per_xcd = (int)((total + attn::kNumXcd - 1) / attn::kNumXcd);
-    p.pairs = (int)((n_tiles + 1) / 2);
-    p.units = (long long)B * Hq * p.pairs;
     p.nsplit = 1;
     return ATTN_OK;
 }
@@ -236,6 +228,19 @@ double fast_critical_path(const attn::Params& p, bool pair, int block_kv, bool c
     return worst;
 }
 
+// The fast kernel's work units: 256-row tiles in pairs, or 128-row tiles.
+void set_tiles(attn::Params& p, bool pair)
+{
+    const int rows = pair ? attn::kFastRowsPair : attn::kFastRows;
+    const long long n_tiles = ((long long)p.N + rows - 1) / rows;
+    const long long total = (long long)p.B * p.Hq * n_tiles;
+    p.n_tiles = (int)n_tiles;
+    p.total_wg = (int)total;
+    p.per_xcd = (int)((total + attn::kNumXcd - 1) / attn::kNumXcd);
+    p.pairs = (int)(pair ? n_tiles : (n_tiles + 1) / 2);
+    p.units = (long long)p.B * p.Hq * p.pairs;
+}
+
 // Enqueues a prepared, validated, non-empty call on stream s.
 int launch(Call& cl, const void* q, const void* k, const void* v, float* out, float* lse,
            uint32_t* counts, uint32_t* gap_hist, uint32_t* blk_zero, int nbins, void* ws,
@@ -264,35 +269,49 @@ int launch(Call& cl, const void* q, const void* k, const void* v, float* out, fl
     // below the E4M3 range limit (it does not saturate)
     const bool pow2 = is_pow2_scale(S) && S <= 256.0f;
     const int scale = cl.dyn ? attn::kScaleDynamic : pow2 ? attn::kScalePow2 : attn::kScaleAny;
-    if (cl.prefill) {
-        e = attn::launch_prefill(p, cl.d, cl.block_kv, cl.causal, cl.count, scale,
-                                 cl.mode == ATTN_MODE_FP8QK, n_cu, ws, ws_bytes, s);
+    const bool qk8 = cl.mode == ATTN_MODE_FP8QK;
+    // The fast kernel's causal rows start at a block boundary: a chunk that
+    // starts inside a block is preceded by row_lo empty rows (fewer than a block).
+    attn::Params fp = p;
+    if (cl.causal) {
+        fp.row_lo = p.qoff % cl.block_kv;
+        fp.qoff = p.qoff - fp.row_lo;
+        fp.N = p.N + fp.row_lo;
+    }
+    set_tiles(fp, false);
+    // Kernel and schedule.  Fewer than 128 queries against a cache: the
+    // KV-cache kernel.  Otherwise 256-row tiles in causal-balanced pairs on the
+    // fast kernel, unless the caller asked otherwise or their units leave CUs
+    // idle: then the shortest, by their models, of those, the 128-row schedule
+    // (one tile per unit, two waves per 32-row group) and the KV-cache kernel.
+    // A path of the fast kernel costs 6.5 us and, per phase of a block of 128
+    // keys at d = 128, 1.3 (4096 x 4096 keys, 2 heads: 51 us for 39 phases, the
+    // KV-cache kernel 30; 512 x 512, 8 heads, causal: 17 for 7, and 10).
+    bool kv = cl.fast && p.Nk != p.N && p.N < 128;
+    bool pair = cl.tile == 128;
+    const size_t kv_ws = ws && cl.prefill ? ws_bytes : 0;
+    if (cl.fast && !kv && cl.tile == 0 && fp.units < n_cu) {
+        const double t256 = fast_critical_path(fp, false, cl.block_kv, cl.causal, n_cu);
+        const double t128 = fast_critical_path(fp, true, cl.block_kv, cl.causal, n_cu);
+        pair = t128 < t256;
+        const double phase = (0.25 + 1.05 * cl.block_kv / 128 * (cl.d == 64 ? 0.6 : qk8 ? 0.8 : 1.0)) *
+                             (cl.count ? 1.17 : 1.0);
+        kv = !gap_hist && attn::prefill_time_us(p, cl.d, cl.block_kv, cl.causal, qk8, n_cu, kv_ws) <
+                              6.5 + phase * std::min(t128, t256);
+    }
+    if (kv) {
+        e = attn::launch_prefill(p, cl.d, cl.block_kv, cl.causal, cl.count, scale, qk8, n_cu, kv_ws ? ws : nullptr,
+                                 kv_ws, s);
     } else if (cl.fast) {
-        // Schedule: 256-row tiles in causal-balanced pairs, unless the caller
-        // asked otherwise or their units leave CUs idle and the 128-row
-        // schedule (one tile per unit, two waves per 32-row group) has the
-        // shorter critical path.
-        bool pair = cl.tile == 128;
-        if (cl.tile == 0 && p.units < n_cu)
-            pair = fast_critical_path(p, true, cl.block_kv, cl.causal, n_cu) <
-                   fast_critical_path(p, false, cl.block_kv, cl.causal, n_cu);
-        if (pair) {
-            const long long n_tiles = ((long long)p.N + attn::kFastRowsPair - 1) / attn::kFastRowsPair;
-            const long long total = (long long)p.B * p.Hq * n_tiles;
-            p.n_tiles = (int)n_tiles;
-            p.total_wg = (int)total;
-            p.per_xcd = (int)((total + attn::kNumXcd - 1) / attn::kNumXcd);
-            p.pairs = (int)n_tiles;
-            p.units = total;
-        }
+        if (pair)
+            set_tiles(fp, true);
         // persistent grid: one workgroup per CU (the LDS footprint admits no
         // second one), 8 XCDs, never more workgroups than work units
         const long long per_xcd_max = n_cu >= attn::kNumXcd ? n_cu / attn::kNumXcd : 1;
-        const long long per_xcd = p.units / attn::kNumXcd + 1 < per_xcd_max ? p.units / attn::kNumXcd + 1
-                                                                            : per_xcd_max;
+        const long long per_xcd = fp.units / attn::kNumXcd + 1 < per_xcd_max ? fp.units / attn::kNumXcd + 1
+                                                                             : per_xcd_max;
         const int grid = (int)(per_xcd * attn::kNumXcd);
-        const bool qk8 = cl.mode == ATTN_MODE_FP8QK;
-        auto go = [&](auto fn) { return fn(p, grid, cl.d, cl.block_kv, cl.causal, cl.count, scale, s); };
+        auto go = [&](auto fn) { return fn(fp, grid, cl.d, cl.block_kv, cl.causal, cl.count, scale, s); };
         e = qk8 ? (pair ? go(attn::launch_fast_t<true, true>) : go(attn::launch_fast_t<true, false>))
                 : (pair ? go(attn::launch_fast_t<false, true>) : go(attn::launch_fast_t<false, false>));
     } else {

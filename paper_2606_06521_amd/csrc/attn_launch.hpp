@@ -34,6 +34,8 @@ constexpr int kFastRowsPair = 128;
 // workspace fields of p
 hipError_t launch_prefill(const Params& p, int d, int block_kv, bool causal, bool count, int scale,
                           bool qk8, int n_cu, void* ws, size_t ws_bytes, hipStream_t stream);
+// its expected time (us), for the choice between it and the fast kernel
+double prefill_time_us(const Params& p, int d, int block_kv, bool causal, bool qk8, int n_cu, size_t ws_bytes);
 // One launch of the KV-cache kernel: phase 0 (unsplit), 1 (range maxima) or 2
 // (the visit per range); cols: workgroups per tile that share its columns (phase
 // 0, TR = 16); QK8 selects E4M3 Q and K, TR the tile height.  Each

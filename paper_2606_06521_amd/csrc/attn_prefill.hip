@@ -113,15 +113,19 @@ void plan_bytes(Plan& pl, int d)
 // The candidates -- 16- or 32-row tiles, unsplit, by two workgroups per tile
 // that share its columns, or by C ranges of its keys -- by their time from
 // what was measured of each part (us, bytes per us):
-// - one launch costs 7, the three of a split 15;
-// - a CU takes 40 000 from HBM (128 CUs: 4.7 TB/s on the decode of 16 requests
-//   x 8 KV heads x 8192 keys) and 75 000 from its L2 (tiles of one head side by
-//   side: 64 queries of 4 x 32 heads against 8192 keys, 49 us), the chip
-//   6 200 000 from HBM;
+// - one launch costs 7, the three of a split 15, and 4 more for every further
+//   generation of workgroups (their start and merge);
 // - every workgroup reads its tile's K (twice in a split: range maxima first)
-//   and V, in rounds of eight blocks; a (batch, KV head)'s keys come from HBM once.
+//   and V, in rounds of eight blocks: 75 000 from the CU's L2 (tiles of one head
+//   side by side: 64 queries of 4 x 32 heads against 8192 keys, 49 us), at least
+//   4.8 (32-row tiles, whose softmax fills the round; 2048 x 2048, 8 heads, E4M3:
+//   31 us) or 2.6 per round of 128-key blocks and 2 (777 x 777, d = 64, blocks of
+//   64: 17 us);
+// - a (batch, KV head)'s keys come from HBM once: 40 000 per CU (decode of 16
+//   requests x 8 KV heads x 8192 keys on 128 CUs: 4.7 TB/s), 6 200 000 in all.
 // C = min(n_cu / units, blocks / 8, 512 / rows): every wave still has a block.
-Plan make_plan(const Params& p, int d, int block_kv, bool causal, bool qk8, int n_cu, size_t ws_bytes)
+Plan make_plan(const Params& p, int d, int block_kv, bool causal, bool qk8, int n_cu, size_t ws_bytes,
+               double* time = nullptr)
 {
     const long long rows = (long long)p.Hq / p.Hkv * p.N;
     // (no tile visits more blocks than this)
@@ -130,11 +134,11 @@ Plan make_plan(const Params& p, int d, int block_kv, bool causal, bool qk8, int 
     const double k_row = qk8 ? d : 2 * d, v_row = d;
     const double head_keys = (double)p.B * p.Hkv * nb * block_kv;
     // one pass over `row` bytes per key on wgs workgroups of `blocks` blocks each
-    auto pass = [&](double wgs, double blocks, double row) {
+    auto pass = [&](int tr, double wgs, double blocks, double row) {
         const double gens = ceil(wgs / n_cu), active = std::min(wgs, (double)n_cu);
-        const double own = ceil(blocks / kWaves) * kWaves * block_kv * row;
-        return std::max(gens * own / 75e3, head_keys * (k_row == row ? k_row : k_row + v_row) /
-                                               std::min(6.2e6, 40e3 * active));
+        const double round = std::max({kWaves * block_kv * row / 75e3, (tr == 32 ? 4.8 : 2.6) * block_kv / 128, 2.0});
+        return std::max(gens * ceil(blocks / kWaves) * round + 4 * (gens - 1),
+                        head_keys * (k_row == row ? k_row : k_row + v_row) / std::min(6.2e6, 40e3 * active));
     };
     Plan best{};
     double t_best = 0;
@@ -151,10 +155,10 @@ Plan make_plan(const Params& p, int d, int block_kv, bool causal, bool qk8, int 
                 t_best = t;
             }
         };
-        take(7 + pass((double)pl.units, (double)nb, k_row + v_row));
+        take(7 + pass(tr, (double)pl.units, (double)nb, k_row + v_row));
         if (tr == 16 && 2 * pl.units <= n_cu) {
             pl.cols = 2;
-            take(7 + pass(2.0 * pl.units, (double)nb, k_row + v_row / 2));
+            take(7 + pass(tr, 2.0 * pl.units, (double)nb, k_row + v_row / 2));
             pl.cols = 1;
         }
         pl.C = std::min({n_cu / pl.units, nb / kWaves, (long long)(kMaxRanges / tr)});
@@ -165,10 +169,12 @@ Plan make_plan(const Params& p, int d, int block_kv, bool causal, bool qk8, int 
         }
         if (pl.C > 1) {
             const double wgs = (double)pl.units * pl.C, blocks = ceil((double)nb / pl.C);
-            take(15 + pass(wgs, blocks, k_row) + pass(wgs, blocks, k_row + v_row));
+            take(15 + pass(tr, wgs, blocks, k_row) + pass(tr, wgs, blocks, k_row + v_row));
         }
     }
     plan_bytes(best, d);
+    if (time)
+        *time = t_best;
     return best;
 }
 
@@ -182,6 +188,13 @@ hipError_t launch_phase(const Params& p, const Plan& pl, int d, int block_kv, bo
 }
 
 }  // namespace
+
+double prefill_time_us(const Params& p, int d, int block_kv, bool causal, bool qk8, int n_cu, size_t ws_bytes)
+{
+    double t = 0;
+    make_plan(p, d, block_kv, causal, qk8, n_cu, ws_bytes, &t);
+    return t;
+}
 
 // The least a caller's workspace has to hold: what a split of 32-row tiles
 // per query head over min(n_cu / tiles, blocks / 8, 8) workgroups takes (a plan

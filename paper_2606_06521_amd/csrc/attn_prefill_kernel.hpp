@@ -474,7 +474,6 @@ __global__ void __launch_bounds__(64 * kKvWaves) kv_kernel(Params p)
             cvt_scale = __uint_as_float((uint32_t)(127 - kj) << 23);
             pv_sb = 127 + p.k0 - kj;
         }
-        const int lim = limit(on && row < rows, t0);   // counts: the valid keys
         float lsum = 0.f;
         uint32_t pk[8 * PVS] = {};
 #pragma unroll
@@ -506,19 +505,34 @@ __global__ void __launch_bounds__(64 * kKvWaves) kv_kernel(Params p)
                 pk[kt * (REGS / 4) + r4] = word;
                 if (COUNT || TR == 32)
                     __builtin_amdgcn_sched_barrier(0);
-                if (COUNT) {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int key = TL::TSTEP * kt + TL::GSTEP * g + 4 * r4 + i;   // in the block
-                        const bool z = ((word >> (8 * i)) & 0xFFu) == 0 && key <= lim;
-                        if (z) {
-                            if (j > 0) ++cnt2;
-                            else if (key < p.n_sink) ++cnt0;
-                            else ++cnt1;
-                        }
-                    }
-                }
             }
+        }
+        if constexpr (COUNT) {
+            // byte i of word (kt, r4) holds the block's key k0 + i; it is valid iff
+            // k0 + i <= lim, and a sink key iff k0 + i < ns (invalid and
+            // other-category bytes are forced non-zero)
+            const int lim = limit(on && row < rows, t0);
+            const int ns = j == 0 ? p.n_sink : 0;
+            auto low_bytes = [](int x) __attribute__((always_inline)) {
+                return (uint32_t)((1ull << (8 * min(max(x, 0), 4))) - 1);
+            };
+            uint32_t z0 = 0, zn = 0;
+#pragma unroll
+            for (int i = 0; i < PW; ++i) {
+                const int k0 = TL::TSTEP * (i / (REGS / 4)) + TL::GSTEP * g + 4 * (i % (REGS / 4));
+                const uint32_t valid = low_bytes(lim - k0 + 1);
+                if (j == 0) {
+                    const uint32_t sink = low_bytes(ns - k0);
+                    z0 += zero_codes(pk[i] | ~(valid & sink));
+                    zn += zero_codes(pk[i] | ~(valid & ~sink));
+                } else {
+                    zn += zero_codes(pk[i] | ~valid);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            cnt0 += z0;
+            cnt1 += j == 0 ? zn : 0u;
+            cnt2 += j == 0 ? 0u : zn;
         }
         ell = alpha * ell + lsum;
         // (alpha is exactly 1 in every lane while no row's maximum moves)

@@ -66,3 +66,43 @@ def test_workspace_sizes():
         log(f"kv workspace {nbytes} of {full}")
         compare(inp, (o, lse, None), "fast", 256.0, "reverse", True, 128, label=f"workspace {nbytes}")
     assert call(ws.data_ptr(), least - 1)[0] == A.ATTN_ERR_INVALID_ARG
+
+
+# (B, Hq, Hkv, Nq, Nk, d, block_kv): the first query lies inside a KV block, in
+# the block's first or last row, or in an earlier block than the wave's other rows
+CHUNKS = [(2, 4, 2, 130, 257, 128, 128), (1, 4, 4, 257, 515, 64, 64), (1, 2, 1, 640, 705, 128, 64),
+          (1, 2, 2, 300, 1003, 64, 128)]
+
+
+@pytest.mark.parametrize("tile", [None, 128, 256])
+@pytest.mark.parametrize("B,Hq,Hkv,nq,nk,d,bc", CHUNKS)
+def test_chunk_that_starts_inside_a_block(B, Hq, Hkv, nq, nk, d, bc, tile):
+    # both schedules of the fast kernel (rows before the chunk are empty) and
+    # whichever kernel the library picks
+    assert (nk - nq) % bc != 0
+    for mode, fmt in (("fast", "bf16_e4m3"), ("fp8qk", "e4m3")):
+        inp = last_queries(make_inputs(B, Hq, Hkv, nk, d, fmt=fmt, delta=8.0, seed=2500 + nk), nq)
+        dev = to_device(inp)
+        for S, order, causal, scale in [(256.0, "reverse", True, "static"), (1.0, "forward", True, "dynamic"),
+                                        (16.0, "reverse", False, "static")]:
+            label = f"chunk {mode} tile={tile} nq={nq} nk={nk} d={d} bc={bc} S={S} {order} {causal}"
+            log(label)
+            gpu = run_gpu(dev, mode, S, order, causal, bc, scale=scale, tile=tile)
+            compare(inp, gpu, mode, S, order, causal, bc, label=label, scale=scale)
+
+
+@pytest.mark.parametrize("H,Hkv,n,d,bc", [(2, 1, 700, 128, 128), (4, 4, 515, 64, 64), (1, 1, 1024, 128, 64)])
+def test_small_square_problems_on_either_kernel(H, Hkv, n, d, bc):
+    # few heads: the library's choice is the KV-cache kernel; its codes are those
+    # of the fast kernel, so the counts are equal on every row
+    for mode, fmt in (("fast", "bf16_e4m3"), ("fp8qk", "e4m3")):
+        inp = make_inputs(1, H, Hkv, n, d, fmt=fmt, delta=8.0, seed=2600 + n)
+        dev = to_device(inp)
+        for order, causal in (("reverse", True), ("forward", False)):
+            label = f"square {mode} n={n} d={d} bc={bc} {order} {causal}"
+            log(label)
+            gpu = run_gpu(dev, mode, 256.0, order, causal, bc)
+            compare(inp, gpu, mode, 256.0, order, causal, bc, label=label)
+            other = run_gpu(dev, mode, 256.0, order, causal, bc, tile=128)
+            assert np.array_equal(gpu[2], other[2]), label
+            assert np.allclose(gpu[0], other[0], rtol=1e-5, atol=1e-6), label
