@@ -2,5 +2,5 @@
 #include "attn_prefill_kernel.hpp"
 
 namespace attn {
-template hipError_t launch_kv_t<true, 16>(const Params&, int, int, bool, int, int, int, hipStream_t);
+template hipError_t launch_kv_t<true, 16>(const Params&, int, int, bool, int, int, int, int, hipStream_t);
 }  // namespace attn

@@ -38,15 +38,15 @@ hipError_t launch_prefill(const Params& p, int d, int block_kv, bool causal, boo
 double prefill_time_us(const Params& p, int d, int block_kv, bool causal, bool qk8, int n_cu, size_t ws_bytes);
 // One launch of the KV-cache kernel: phase 0 (unsplit), 1 (range maxima) or 2
 // (the visit per range); cols: workgroups per tile that share its columns (phase
-// 0, TR = 16); QK8 selects E4M3 Q and K, TR the tile height.  Each
+// 0, TR = 16); waves per workgroup: 8, or 4 (phase 0); QK8 selects E4M3 Q and K, TR the tile height.  Each
 // pair is instantiated in its own translation unit.
 template <bool QK8, int TR>
 hipError_t launch_kv_t(const Params& p, int d, int block_kv, bool count, int scale, int phase, int cols,
-                       hipStream_t s);
-extern template hipError_t launch_kv_t<false, 16>(const Params&, int, int, bool, int, int, int, hipStream_t);
-extern template hipError_t launch_kv_t<true, 16>(const Params&, int, int, bool, int, int, int, hipStream_t);
-extern template hipError_t launch_kv_t<false, 32>(const Params&, int, int, bool, int, int, int, hipStream_t);
-extern template hipError_t launch_kv_t<true, 32>(const Params&, int, int, bool, int, int, int, hipStream_t);
+                       int waves, hipStream_t s);
+extern template hipError_t launch_kv_t<false, 16>(const Params&, int, int, bool, int, int, int, int, hipStream_t);
+extern template hipError_t launch_kv_t<true, 16>(const Params&, int, int, bool, int, int, int, int, hipStream_t);
+extern template hipError_t launch_kv_t<false, 32>(const Params&, int, int, bool, int, int, int, int, hipStream_t);
+extern template hipError_t launch_kv_t<true, 32>(const Params&, int, int, bool, int, int, int, int, hipStream_t);
 // device workspace launch_prefill can use, and the least it accepts (0: none)
 size_t prefill_workspace_bytes(const Params& p, int d, int block_kv, bool causal, bool qk8, int n_cu);
 size_t prefill_workspace_min(const Params& p, int d, int block_kv, bool causal, int n_cu);

@@ -26,7 +26,7 @@ __global__ void __launch_bounds__(128) prefill_merge(Params p)
     if (unit >= p.total_wg / C)
         return;
     const int bk = unit / p.n_tiles;
-    const int tile = unit - bk * p.n_tiles;
+    const int tile = p.causal ? p.n_tiles - 1 - (unit - bk * p.n_tiles) : unit - bk * p.n_tiles;   // as kv_kernel
     const int rows = p.Hq / p.Hkv * p.N;
     const int t = threadIdx.x;
     const int rr = MR * rg + t / PIECES;          // row in the tile
@@ -89,12 +89,12 @@ __global__ void prefill_zero(uint32_t* a, int64_t n)
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-constexpr int kWaves = 8;
 constexpr int kMaxRanges = 512;   // nsplit * tile height (range maxima staged by one workgroup)
 
 struct Plan {
     int rows;              // tile height
     int cols;              // workgroups per tile that share its columns (unsplit tiles)
+    int waves;             // per workgroup
     long long tiles;       // per (batch, KV head)
     long long units;
     long long C;           // workgroups per tile that share its keys
@@ -110,19 +110,23 @@ void plan_bytes(Plan& pl, int d)
     }
 }
 
-// The candidates -- 16- or 32-row tiles, unsplit, by two workgroups per tile
-// that share its columns, or by C ranges of its keys -- by their time from
-// what was measured of each part (us, bytes per us):
-// - one launch costs 7, the three of a split 15, and 4 more for every further
-//   generation of workgroups (their start and merge);
+// The candidates -- 16- or 32-row tiles on workgroups of eight or four waves,
+// unsplit, by two workgroups per tile that share its columns, or by C ranges of
+// its keys -- by their time from what was measured of each part (us, bytes per
+// us):
+// - a launch of eight-wave workgroups costs 7, of four-wave ones 5, the three of
+//   a split 15, and 4 more for every further generation of workgroups (their
+//   start and merge); a CU holds one workgroup of eight waves or two of four;
 // - every workgroup reads its tile's K (twice in a split: range maxima first)
-//   and V, in rounds of eight blocks: 75 000 from the CU's L2 (tiles of one head
-//   side by side: 64 queries of 4 x 32 heads against 8192 keys, 49 us), at least
-//   4.8 (32-row tiles, whose softmax fills the round; 2048 x 2048, 8 heads, E4M3:
-//   31 us) or 2.6 per round of 128-key blocks and 2 (777 x 777, d = 64, blocks of
-//   64: 17 us);
+//   and V, in rounds of a block per wave: 75 000 from the CU's L2 (tiles of one
+//   head side by side: 64 queries of 4 x 32 heads against 8192 keys, 49 us).  A
+//   round of 128-key blocks takes a full CU at least 4.8 on 32-row tiles (their
+//   softmax; 2048 x 2048, 8 heads, E4M3: 31 us), 2.6 on 16-row ones, four waves
+//   alone on their CU 4.0 and 3.0 (the same 64 queries: 69 us), and 2 whatever
+//   the block (777 x 777, d = 64, blocks of 64: 17 us);
 // - a (batch, KV head)'s keys come from HBM once: 40 000 per CU (decode of 16
-//   requests x 8 KV heads x 8192 keys on 128 CUs: 4.7 TB/s), 6 200 000 in all.
+//   requests x 8 KV heads x 8192 keys on 128 CUs: 4.7 TB/s), 33 000 with four
+//   waves on it, 6 200 000 in all.
 // C = min(n_cu / units, blocks / 8, 512 / rows): every wave still has a block.
 Plan make_plan(const Params& p, int d, int block_kv, bool causal, bool qk8, int n_cu, size_t ws_bytes,
                double* time = nullptr)
@@ -134,18 +138,21 @@ Plan make_plan(const Params& p, int d, int block_kv, bool causal, bool qk8, int 
     const double k_row = qk8 ? d : 2 * d, v_row = d;
     const double head_keys = (double)p.B * p.Hkv * nb * block_kv;
     // one pass over `row` bytes per key on wgs workgroups of `blocks` blocks each
-    auto pass = [&](int tr, double wgs, double blocks, double row) {
-        const double gens = ceil(wgs / n_cu), active = std::min(wgs, (double)n_cu);
-        const double round = std::max({kWaves * block_kv * row / 75e3, (tr == 32 ? 4.8 : 2.6) * block_kv / 128, 2.0});
-        return std::max(gens * ceil(blocks / kWaves) * round + 4 * (gens - 1),
-                        head_keys * (k_row == row ? k_row : k_row + v_row) / std::min(6.2e6, 40e3 * active));
+    auto pass = [&](const Plan& pl, double wgs, double blocks, double row) {
+        const double per_cu = 8 / pl.waves, gens = ceil(wgs / (n_cu * per_cu));
+        const double here = std::min(ceil(wgs / n_cu), per_cu), active = std::min(wgs, (double)n_cu);
+        const bool maxima = row == k_row, solo = here < per_cu;
+        const double full = maxima ? 0 : pl.rows == 32 ? 4.8 : 2.6, alone = pl.rows == 32 ? 4.0 : 3.0;
+        const double round = std::max({here * pl.waves * block_kv * row / 75e3, full * here / per_cu * block_kv / 128,
+                                       solo ? alone * block_kv / 128 : 0, 2.0});
+        return std::max(gens * ceil(blocks / pl.waves) * round + 4 * (gens - 1),
+                        head_keys * (maxima ? k_row : k_row + v_row) / std::min(6.2e6, (solo ? 33e3 : 40e3) * active));
     };
     Plan best{};
     double t_best = 0;
     for (int tr = 16; tr <= (rows > 16 ? 32 : 16); tr *= 2) {
         Plan pl{};
         pl.rows = tr;
-        pl.cols = 1;
         pl.C = 1;
         pl.tiles = (rows + tr - 1) / tr;
         pl.units = (long long)p.B * p.Hkv * pl.tiles;
@@ -155,13 +162,18 @@ Plan make_plan(const Params& p, int d, int block_kv, bool causal, bool qk8, int 
                 t_best = t;
             }
         };
-        take(7 + pass(tr, (double)pl.units, (double)nb, k_row + v_row));
-        if (tr == 16 && 2 * pl.units <= n_cu) {
-            pl.cols = 2;
-            take(7 + pass(tr, 2.0 * pl.units, (double)nb, k_row + v_row / 2));
+        for (pl.waves = 8; pl.waves >= 4; pl.waves /= 2) {
+            const double launch = pl.waves == 8 ? 7 : 5;
             pl.cols = 1;
+            take(launch + pass(pl, (double)pl.units, (double)nb, k_row + v_row));
+            if (tr == 16 && 2 * pl.units <= n_cu) {
+                pl.cols = 2;
+                take(launch + pass(pl, 2.0 * pl.units, (double)nb, k_row + v_row / 2));
+            }
         }
-        pl.C = std::min({n_cu / pl.units, nb / kWaves, (long long)(kMaxRanges / tr)});
+        pl.waves = 8;
+        pl.cols = 1;
+        pl.C = std::min({n_cu / pl.units, nb / pl.waves, (long long)(kMaxRanges / tr)});
         for (; pl.C > 1; --pl.C) {
             plan_bytes(pl, d);
             if (pl.bytes <= ws_bytes)
@@ -169,7 +181,7 @@ Plan make_plan(const Params& p, int d, int block_kv, bool causal, bool qk8, int 
         }
         if (pl.C > 1) {
             const double wgs = (double)pl.units * pl.C, blocks = ceil((double)nb / pl.C);
-            take(15 + pass(tr, wgs, blocks, k_row) + pass(tr, wgs, blocks, k_row + v_row));
+            take(15 + pass(pl, wgs, blocks, k_row) + pass(pl, wgs, blocks, k_row + v_row));
         }
     }
     plan_bytes(best, d);
@@ -181,7 +193,7 @@ Plan make_plan(const Params& p, int d, int block_kv, bool causal, bool qk8, int 
 hipError_t launch_phase(const Params& p, const Plan& pl, int d, int block_kv, bool count, int scale, bool qk8,
                         int phase, hipStream_t s)
 {
-    auto go = [&](auto fn) { return fn(p, d, block_kv, count, scale, phase, pl.cols, s); };
+    auto go = [&](auto fn) { return fn(p, d, block_kv, count, scale, phase, pl.cols, pl.waves, s); };
     if (pl.rows == 16)
         return qk8 ? go(launch_kv_t<true, 16>) : go(launch_kv_t<false, 16>);
     return qk8 ? go(launch_kv_t<true, 32>) : go(launch_kv_t<false, 32>);
@@ -206,10 +218,10 @@ size_t prefill_workspace_min(const Params& p, int d, int block_kv, bool causal, 
                                 : ((long long)p.Nk + block_kv - 1) / block_kv;
     if (units >= n_cu)
         return 0;
-    const long long C = std::min({n_cu / units, nb / kWaves, 8LL});
+    const long long C = std::min({n_cu / units, nb / 8, 8LL});
     if (C <= 1)
         return 0;
-    return align256((size_t)units * C * kWaves * 32 * sizeof(float)) +
+    return align256((size_t)units * C * 8 * 32 * sizeof(float)) +
            align256((size_t)units * C * (32 * (size_t)d + 32) * sizeof(float));
 }
 

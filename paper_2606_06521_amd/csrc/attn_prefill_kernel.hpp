@@ -8,8 +8,8 @@
 // head R / Nq) cut into tiles of TR = 16 or 32 rows: a decode step with four
 // query heads per KV head reads each key once instead of four times.
 //
-// A tile's workgroup has eight waves.  They take the KV blocks of the visit in
-// rounds, wave w the block at visit position 8 i + w of round i.  Each wave
+// A tile's workgroup has NW = 8 or 4 waves.  They take the KV blocks of the visit
+// in rounds, wave w the block at visit position NW i + w of round i.  Each wave
 // takes the row maxima of its block's scores and puts them in LDS; after the
 // round's one barrier the running maximum the sequential visit has reached at
 // that block is the maximum over the earlier rounds (carried by every wave)
@@ -112,16 +112,13 @@ struct KvTile<16, BC> {
     }
 };
 
-constexpr int kKvWaves = 8;
-
 }  // namespace
 
-template <int D, int BC, bool COUNT, int SCALE, bool QK8, int TR, int PHASE, int DS>
-__global__ void __launch_bounds__(64 * kKvWaves) kv_kernel(Params p)
+template <int D, int BC, bool COUNT, int SCALE, bool QK8, int TR, int PHASE, int DS, int NW>
+__global__ void __launch_bounds__(64 * NW, 2) kv_kernel(Params p)
 {
     using TL = KvTile<TR, BC>;
     using Acc = typename TL::Acc;
-    constexpr int NW = kKvWaves;
     constexpr int NG = TL::NG, REGS = TL::REGS;
     constexpr int KT = BC / TR;                 // S^T tiles per block
     constexpr int DO = D / DS;                  // columns of O in this workgroup
@@ -185,7 +182,8 @@ __global__ void __launch_bounds__(64 * kKvWaves) kv_kernel(Params p)
     const int colp = DS == 1 ? 0 : unit % DS;
     unit /= DS;
     const int bk = unit / p.n_tiles;            // (batch, KV head)
-    const int tile = unit - bk * p.n_tiles;
+    // (causal: the tiles with the most blocks start first)
+    const int tile = p.causal ? p.n_tiles - 1 - (unit - bk * p.n_tiles) : unit - bk * p.n_tiles;
     const int Nq = p.N, Nk = p.Nk, qoff = p.qoff;
     const int rows = p.Hq / p.Hkv * Nq;         // query rows of the group
     const bool causal = p.causal != 0;
@@ -681,39 +679,45 @@ __global__ void __launch_bounds__(64 * kKvWaves) kv_kernel(Params p)
 namespace {
 
 template <int D, int BC, bool COUNT, bool QK8, int TR>
-hipError_t kv_launch(const Params& p, int scale, int phase, int cols, hipStream_t s)
+hipError_t kv_launch(const Params& p, int scale, int phase, int cols, int waves, hipStream_t s)
 {
     auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(p.per_xcd * kNumXcd), dim3(64 * kKvWaves), 0, s, p);
+        hipLaunchKernelGGL(kern, dim3(p.per_xcd * kNumXcd), dim3(64 * waves), 0, s, p);
         return hipGetLastError();
     };
-    auto by_scale = [&](auto ph, auto ds) {
-        constexpr int PH = decltype(ph)::value, DS = decltype(ds)::value;
-        return scale == kScaleDynamic ? go(kv_kernel<D, BC, COUNT, kScaleDynamic, QK8, TR, PH, DS>)
-               : scale == kScalePow2  ? go(kv_kernel<D, BC, COUNT, kScalePow2, QK8, TR, PH, DS>)
-                                      : go(kv_kernel<D, BC, COUNT, kScaleAny, QK8, TR, PH, DS>);
+    auto by_scale = [&](auto ph, auto ds, auto nw) {
+        constexpr int PH = decltype(ph)::value, DS = decltype(ds)::value, NW = decltype(nw)::value;
+        return scale == kScaleDynamic ? go(kv_kernel<D, BC, COUNT, kScaleDynamic, QK8, TR, PH, DS, NW>)
+               : scale == kScalePow2  ? go(kv_kernel<D, BC, COUNT, kScalePow2, QK8, TR, PH, DS, NW>)
+                                      : go(kv_kernel<D, BC, COUNT, kScaleAny, QK8, TR, PH, DS, NW>);
     };
     using std::integral_constant;
+    constexpr integral_constant<int, 0> unsplit{};
+    constexpr integral_constant<int, 1> one{};
+    constexpr integral_constant<int, 2> two{};
+    constexpr integral_constant<int, 4> w4{};
+    constexpr integral_constant<int, 8> w8{};
     if (phase == 1)   // only maxima: one instantiation, whatever the scale and diagnostics
-        return go(kv_kernel<D, BC, false, kScaleAny, QK8, TR, 1, 1>);
+        return go(kv_kernel<D, BC, false, kScaleAny, QK8, TR, 1, 1, 8>);
     if (phase == 2)
-        return by_scale(integral_constant<int, 2>{}, integral_constant<int, 1>{});
+        return by_scale(two, one, w8);
     if constexpr (TR == 16) {
         if (cols == 2)
-            return by_scale(integral_constant<int, 0>{}, integral_constant<int, 2>{});
+            return waves == 4 ? by_scale(unsplit, two, w4) : by_scale(unsplit, two, w8);
     }
-    return by_scale(integral_constant<int, 0>{}, integral_constant<int, 1>{});
+    return waves == 4 ? by_scale(unsplit, one, w4) : by_scale(unsplit, one, w8);
 }
 
 }  // namespace
 
 template <bool QK8, int TR>
-hipError_t launch_kv_t(const Params& p, int d, int block_kv, bool count, int scale, int phase, int cols, hipStream_t s)
+hipError_t launch_kv_t(const Params& p, int d, int block_kv, bool count, int scale, int phase, int cols, int waves,
+                       hipStream_t s)
 {
     auto pick = [&](auto dc, auto bc) {
         constexpr int D = decltype(dc)::value, BC = decltype(bc)::value;
-        return count ? kv_launch<D, BC, true, QK8, TR>(p, scale, phase, cols, s)
-                     : kv_launch<D, BC, false, QK8, TR>(p, scale, phase, cols, s);
+        return count ? kv_launch<D, BC, true, QK8, TR>(p, scale, phase, cols, waves, s)
+                     : kv_launch<D, BC, false, QK8, TR>(p, scale, phase, cols, waves, s);
     };
     using std::integral_constant;
     if (d == 64)

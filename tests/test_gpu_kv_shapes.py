@@ -1,5 +1,5 @@
-"""The KV-cache kernel's plans (16- or 32-row tiles of a group's query rows,
-unsplit, by columns, or over ranges of the keys), each at lengths that leave
+"""The KV-cache kernel's plans (16- or 32-row tiles of a group's query rows, four
+or eight waves, unsplit, by columns, or over ranges of the keys), each at lengths that leave
 partial tiles, partial last blocks, rounds with idle waves and tiles that hold
 rows of several query heads, against the oracle on every row; and workspaces
 between the least and the reported size."""
@@ -15,11 +15,13 @@ pytestmark = pytest.mark.gpu
 # (B, Hq, Hkv, Nq, Nk, d, block_kv): the plan on 256 compute units
 SHAPES = [
     (1, 8, 2, 1, 20000, 128, 128),     # 16 rows, 19 ranges of the keys
-    (1, 8, 8, 3, 515, 64, 64),         # 16 rows, two workgroups by columns
-    (2, 16, 4, 8, 1501, 128, 64),      # the same, rows of two heads per tile
-    (60, 8, 4, 4, 333, 64, 128),       # 16 rows, unsplit
-    (40, 8, 8, 40, 300, 128, 128),     # 32 rows, unsplit
-    (40, 8, 8, 37, 261, 64, 64),       # the same
+    (1, 8, 8, 3, 515, 64, 64),         # 16 rows, eight waves
+    (2, 16, 4, 8, 1501, 128, 64),      # 16 rows, two workgroups by columns, rows of two heads per tile
+    (1, 8, 4, 8, 200, 128, 64),        # 16 rows, four waves, by columns
+    (60, 8, 4, 4, 333, 64, 128),       # 16 rows, four waves
+    (40, 8, 8, 37, 261, 64, 64),       # the same in two generations
+    (16, 8, 8, 33, 1300, 128, 128),    # 32 rows, four waves
+    (16, 8, 8, 60, 2600, 128, 128),    # 32 rows, eight waves
     (1, 16, 1, 120, 12001, 128, 128),  # 32 rows, 4 ranges, rows of up to two heads per tile
 ]
 
