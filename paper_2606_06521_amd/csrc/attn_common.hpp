@@ -45,9 +45,7 @@ struct Params {
     int B, Hq, Hkv, N;   // N: query rows per (batch, head)
     int Nk;              // cached keys per (batch, kv head); N for self-attention
     int qoff;            // Nk - N: query row r sits at key position r + qoff
-    int row_lo;          // fast kernel: rows before this one only pad a chunk to a block boundary
     int order;           // 0 forward, 1 reverse
-    int causal;          // faithful kernel (the fast kernels take it as a template argument)
     int n_sink;
     float S;             // static P-scale (2^k0 with the dynamic scale)
     float inv_S;         // 1/S, used only when S is a power of two (exact)
@@ -61,11 +59,13 @@ struct Params {
     // tiles (t, n_tiles - 1 - t) of one (batch, head)
     int pairs;           // units per (batch, head) = ceil(n_tiles / 2)
     long long units;     // B * Hq * pairs
-    // prefill kernel split over several workgroups per 32-row tile (nsplit
-    // > 1); the workspace is owned by the launcher for the duration of a call
-    int nsplit;          // workgroups per tile (1: one fused workgroup)
-    float* ws_max;       // [tile][nsplit * waves][32] row maxima of each wave range
-    float* ws_part;      // [tile][nsplit][32 * d + 32] each workgroup's O sum, then l
+    // KV-cache kernel: a tile's keys split over several workgroups (nsplit > 1);
+    // the workspace is the caller's
+    int nsplit;          // workgroups per tile (1: unsplit)
+    float* ws_max;       // [tile][nsplit][rows] row maxima of each range
+    float* ws_part;      // [tile][nsplit][rows * d + rows] each workgroup's O sum, then l
+    int causal;          // faithful and KV-cache kernels (the fast kernel takes it as a template argument)
+    int row_lo;          // fast kernel: rows before this one only pad a chunk to a block boundary
 };
 
 // how the fast kernel applies the P-scale

@@ -13,8 +13,15 @@ namespace fast_dispatch {
 template <int D, int BC, bool CAUSAL, bool COUNT, int SCALE, bool QK8, bool PAIR>
 hipError_t launch_one(const Params& p, int grid, hipStream_t stream)
 {
-    hipLaunchKernelGGL((fast_kernel<D, BC, CAUSAL, COUNT, SCALE, QK8, PAIR>), dim3(grid), dim3(512), 0, stream, p);
-    return hipGetLastError();
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(512), 0, stream, p);
+        return hipGetLastError();
+    };
+    if constexpr (CAUSAL) {
+        if (p.row_lo != 0)
+            return go(fast_kernel<D, BC, CAUSAL, COUNT, SCALE, QK8, PAIR, true>);
+    }
+    return go(fast_kernel<D, BC, CAUSAL, COUNT, SCALE, QK8, PAIR, false>);
 }
 
 template <int D, int BC, bool CAUSAL, bool COUNT, bool QK8, bool PAIR>

@@ -127,7 +127,7 @@ __device__ inline i32x2 lds_read_tr8(const uint8_t* p)
 // to the row's final maximum and added at the end of the tile.  Each tile is
 // one work unit (no pairing), which fills the chip when 256-row tiles leave
 // CUs idle.
-template <int D, int BC, bool CAUSAL, bool COUNT, int SCALE, bool QK8, bool PAIR>
+template <int D, int BC, bool CAUSAL, bool COUNT, int SCALE, bool QK8, bool PAIR, bool LO>
 __global__ void __launch_bounds__(512) fast_kernel(Params p)
 {
     constexpr int NW = 8;
@@ -184,8 +184,10 @@ __global__ void __launch_bounds__(512) fast_kernel(Params p)
         // r + qoff.  Under causal masking qoff is a multiple of BC, so that
         // every row of a wave lies in one BC-block of key positions: a chunk
         // that starts inside a block is preceded by lo rows that are neither
-        // loaded nor stored.
-        const int N = p.N, Nk = p.Nk, qoff = p.qoff, lo = CAUSAL ? p.row_lo : 0;
+        // loaded nor stored (q, out, lse and counts point lo rows before the
+        // first one's).  LO: there are such rows; a kernel of its own, since the
+        // extra row checks cost the others 1.5 % at blocks of 64 keys.
+        const int N = p.N, Nk = p.Nk, qoff = p.qoff, lo = LO ? p.row_lo : 0;
         const int b = bh / p.Hq;
         const int hq = bh - b * p.Hq;
         const int hk = hq / (p.Hq / p.Hkv);
@@ -199,16 +201,16 @@ __global__ void __launch_bounds__(512) fast_kernel(Params p)
         const int wrow0 = row0 + 32 * (PAIR ? (w & 3) : w);
         const int row = wrow0 + n;
 
-        const bool row_ok = row >= lo && row < N;
-        const size_t head_row0 = (size_t)bh * (N - lo);           // the head's first row in q, out, lse and counts
-        const uint8_t* Qg = static_cast<const uint8_t*>(p.q) + head_row0 * KROW;
+        auto row_ok = [&]() __attribute__((always_inline)) { return (!LO || row >= lo) && row < N; };
+        const int nrow = N - lo;                     // rows per head in memory
+        const uint8_t* Qg = static_cast<const uint8_t*>(p.q) + (size_t)bh * nrow * KROW;
         const size_t kvrow0 = ((size_t)b * p.Hkv + hk) * (size_t)Nk;
         const uint8_t* Kg = static_cast<const uint8_t*>(p.k) + kvrow0 * KROW;
         const uint8_t* Vg = static_cast<const uint8_t*>(p.v) + kvrow0 * D;
 
         const int last_row_wg = min(row0 + BM, N) - 1;
         const int nb = CAUSAL ? (last_row_wg + qoff) / BC + 1 : (Nk + BC - 1) / BC;
-        const bool wave_on = wrow0 < N && wrow0 + 31 >= lo;
+        const bool wave_on = wrow0 < N && (!LO || wrow0 + 31 >= lo);
         // every row of a wave lies in one BC-block of rows (BC is a multiple of 32)
         const int nblk_w = CAUSAL ? (min(wrow0 + 31, N - 1) + qoff) / BC + 1 : nb;
         auto jof = [&](int k) __attribute__((always_inline)) { return p.order == 0 ? k : nb - 1 - k; };
@@ -275,8 +277,8 @@ __global__ void __launch_bounds__(512) fast_kernel(Params p)
         using QFrag = std::conditional_t<QK8, i32x8, bf16x8>;
         constexpr int QSTEP = QK8 ? 64 : 32;    // bytes of a Q row per k-step
         QFrag qf[DK];
-        if (row_ok) {
-            const uint8_t* qr = Qg + (size_t)(row - lo) * KROW;
+        if (row_ok()) {
+            const uint8_t* qr = Qg + (size_t)row * KROW;
 #pragma unroll
             for (int kk = 0; kk < DK; ++kk)
                 qf[kk] = *reinterpret_cast<const QFrag*>(qr + QSTEP * kk + (QSTEP / 2) * h);
@@ -480,7 +482,7 @@ __global__ void __launch_bounds__(512) fast_kernel(Params p)
             const float mc_new = m_new * c;
             const float alpha = __builtin_amdgcn_exp2f(mc_run - mc_new);
             const float nmc = -mc_new;
-            if (COUNT && p.gap_hist && h == 0 && row_ok)
+            if (COUNT && p.gap_hist && h == 0 && row_ok())
                 record_gap(p, bh, j, mx, c, nmc);
             // Dynamic P-scale (Limitations and Future Work, read as: the
             // block's largest P lands in (S/2, S]): kj = k0 + clamp(floor(-xmax),
@@ -598,7 +600,7 @@ __global__ void __launch_bounds__(512) fast_kernel(Params p)
                     cnt0 += z0;
                     cnt1 += zn;
                 }
-                bz += row_ok ? z0 + zn : 0u;
+                bz += row_ok() ? z0 + zn : 0u;
             }
             if (COUNT && !slow_count) {
                 uint32_t zc = 0;
@@ -608,7 +610,7 @@ __global__ void __launch_bounds__(512) fast_kernel(Params p)
                     for (int r4 = 0; r4 < 4; ++r4)
                         zc += zero_codes(pk[kt][r4]);
                 cnt2 += zc;
-                bz += row_ok ? zc : 0u;
+                bz += row_ok() ? zc : 0u;
             }
             if (COUNT && p.blk_zero)
                 record_block_zeros(p, bh, j, bz);
@@ -816,8 +818,7 @@ __global__ void __launch_bounds__(512) fast_kernel(Params p)
                                              32u * (x >> 1));
                 const uint32_t rr = (uint32_t)lane >> 3, cc = (uint32_t)lane & 7u;
                 const uint32_t ra = lds_base(base_w + 128u * rr + 16u * (cc ^ rr));
-                const int r0 = wrow0 + (int)rr;
-                float* const orow0 = p.out + ((long long)head_row0 + r0 - lo) * D + 4 * cc;
+                float* const orow0 = p.out + ((size_t)bh * nrow + wrow0 + rr) * D + 4 * cc;
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) {
 #pragma unroll
@@ -832,14 +833,14 @@ __global__ void __launch_bounds__(512) fast_kernel(Params p)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         const f32x4 v4 = lds_load<f32x4>(ra + 1024u * i);
-                        if (r0 + 8 * i >= lo && r0 + 8 * i < N)
+                        if ((!LO || wrow0 + 8 * i + (int)rr >= lo) && wrow0 + 8 * i + (int)rr < N)
                             *reinterpret_cast<f32x4*>(orow0 + (size_t)8 * i * D + 32 * dt) = v4;
                     }
                 }
             }
         }
-        if (row_ok) {
-            const size_t flat = head_row0 + (row - lo);
+        if (row_ok()) {
+            const size_t flat = (size_t)bh * nrow + row;
             if (!STAGED_OUT && p.out) {
                 const float inv = p.v_descale / (S * ell_row);
                 float* orow = p.out + flat * D;

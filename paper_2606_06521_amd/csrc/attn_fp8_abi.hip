@@ -277,6 +277,11 @@ int launch(Call& cl, const void* q, const void* k, const void* v, float* out, fl
         fp.row_lo = p.qoff % cl.block_kv;
         fp.qoff = p.qoff - fp.row_lo;
         fp.N = p.N + fp.row_lo;
+        const ptrdiff_t lo = fp.row_lo;
+        fp.q = static_cast<const uint8_t*>(p.q) - lo * cl.d * (qk8 ? 1 : 2);
+        fp.out = p.out ? p.out - lo * cl.d : nullptr;
+        fp.lse = p.lse ? p.lse - lo : nullptr;
+        fp.counts = p.counts ? p.counts - 3 * lo : nullptr;
     }
     set_tiles(fp, false);
     // Kernel and schedule.  Fewer than 128 queries against a cache: the
