@@ -9,61 +9,75 @@
 
 namespace attn {
 
-// Merge of a split tile: workgroup (unit, g) of 128 threads takes MR = 512 / D
-// rows of the tile, one 16-byte piece of a row per thread; the nsplit partial
-// sums are added in a fixed order and divided by S l.  lse comes from the
-// tile's final row maxima (the largest of its range maxima).
+// Merge of a split tile: one workgroup of 256 threads per row; thread (piece,
+// part) takes one 16-byte piece of the row from every PARTS-th of the nsplit
+// partial sums, all requested at once, and the PARTS sums are added through LDS
+// (a fixed order).  lse comes from the row's final maximum (the largest of its
+// range maxima).  What bounds it is latency -- one round of loads, one of LDS:
+// 32 partial sums of 32 rows 6.2 us with one thread per piece (four rounds of
+// eight loads), 3.6 so.
 template <int D, int TR>
-__global__ void __launch_bounds__(128) prefill_merge(Params p)
+__global__ void __launch_bounds__(256) prefill_merge(Params p)
 {
     constexpr int PART = TR * D + TR;
     constexpr int PIECES = D / 4;               // 16-byte pieces per row
-    constexpr int MR = 128 / PIECES;            // rows per workgroup
-    constexpr int GROUPS = TR / MR;
-    const int unit = blockIdx.x / GROUPS;
-    const int rg = blockIdx.x % GROUPS;
+    constexpr int PARTS = 256 / PIECES;
+    constexpr int CMAX = 512 / TR;              // largest nsplit
+    constexpr int PER = (CMAX + PARTS - 1) / PARTS;
+    __shared__ f32x4 osh[PARTS][PIECES];
+    __shared__ float lsh[PARTS], msh[PARTS];
     const int C = p.nsplit;
+    const int unit = blockIdx.x / TR, rr = blockIdx.x % TR;
     if (unit >= p.total_wg / C)
         return;
     const int bk = unit / p.n_tiles;
     const int tile = p.causal ? p.n_tiles - 1 - (unit - bk * p.n_tiles) : unit - bk * p.n_tiles;   // as kv_kernel
     const int rows = p.Hq / p.Hkv * p.N;
-    const int t = threadIdx.x;
-    const int rr = MR * rg + t / PIECES;          // row in the tile
-    const int piece = t % PIECES;
     const int row = TR * tile + rr;
     if (row >= rows)
         return;
+    const int piece = threadIdx.x % PIECES, part = threadIdx.x / PIECES;
     const float* base = p.ws_part + (size_t)unit * C * PART;
-    f32x4 acc = {};
-    float l = 0.f;
-    // the tile's final maximum (for lse): requested with the partial sums
-    // (exact in any order)
-    float m = -INFINITY;
     const float* mx = p.ws_max + (size_t)unit * C * TR + rr;
-    for (int c0 = 0; c0 < C; c0 += 8) {
-        f32x4 part[8];
-        float lp[8], mp[8];
+    f32x4 x[PER];
+    float lp[PER], mp[PER];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            if (c0 + u < C) {
-                const float* b = base + (size_t)(c0 + u) * PART;
-                part[u] = *reinterpret_cast<const f32x4*>(b + rr * D + 4 * piece);
-                lp[u] = b[TR * D + rr];
-                mp[u] = mx[(c0 + u) * TR];
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            if (c0 + u < C) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    acc[i] += part[u][i];
-                l += lp[u];
-                m = fmax_f(m, mp[u]);
-            }
-        }
+    for (int i = 0; i < PER; ++i) {
+        const int c = part + PARTS * i;
+        const bool on = c < C;
+        const float* b = base + (size_t)(on ? c : 0) * PART;
+        x[i] = on ? *reinterpret_cast<const f32x4*>(b + rr * D + 4 * piece) : f32x4{};
+        lp[i] = on ? b[TR * D + rr] : 0.f;
+        mp[i] = on ? mx[c * TR] : -INFINITY;
     }
+    f32x4 acc = x[0];
+    float l = lp[0], m = mp[0];
+#pragma unroll
+    for (int i = 1; i < PER; ++i) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            acc[e] += x[i][e];
+        l += lp[i];
+        m = fmax_f(m, mp[i]);
+    }
+    osh[part][piece] = acc;
+    if (piece == 0) {
+        lsh[part] = l;
+        msh[part] = m;
+    }
+    __syncthreads();
+    if (part != 0)
+        return;
+#pragma unroll
+    for (int v = 1; v < PARTS; ++v) {
+        const f32x4 t = osh[v][piece];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            acc[e] += t[e];
+        l += lsh[v];
+        m = fmax_f(m, msh[v]);
+    }
+    // (l and m of part 0 are the same in all its pieces)
     const size_t flat = (size_t)bk * rows + row;
     if (p.out) {
         const float inv = p.v_descale / (p.S * l);
@@ -262,9 +276,8 @@ hipError_t launch_prefill(const Params& p_in, int d, int block_kv, bool causal, 
     if (e == hipSuccess)
         e = launch_phase(p, pl, d, block_kv, count, scale, qk8, 2, stream);
     if (e == hipSuccess) {
-        // 512 / d rows per workgroup
-        const dim3 grid((unsigned)(pl.units * pl.rows * d / 512));
-        auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(128), 0, stream, p); };
+        const dim3 grid((unsigned)(pl.units * pl.rows));
+        auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(256), 0, stream, p); };
         if (pl.rows == 16)
             d == 64 ? go(prefill_merge<64, 16>) : go(prefill_merge<128, 16>);
         else
