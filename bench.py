@@ -43,6 +43,7 @@ KERNEL_SOURCES = ["paper_2606_06521_amd/csrc/attn_fast_kernel.hpp",
                   "paper_2606_06521_amd/csrc/attn_fast_qk8.hip",
                   "paper_2606_06521_amd/csrc/attn_fast_qk8_pair.hip",
                   "paper_2606_06521_amd/csrc/attn_prefill.hip",
+                  "paper_2606_06521_amd/csrc/attn_prefill_kernel.hpp",
                   "paper_2606_06521_amd/csrc/attn_common.hpp"]
 HBM_PEAK_GBS = 8000.0
 # chip-wide v_exp_f32 rate measured by tests/test_gpu_probes.py::test_exp2_issue_rate
@@ -115,11 +116,16 @@ def write_traffic(fetch_csv: str, write_csv: str, workload: str, copy_mib: int =
     def read(path):
         rows = list(csv.DictReader(open(path)))
         name = lambda r: r["Kernel_Name"]
+        kv = lambda n, want: "kv_kernel<" in n and want(n.split("kv_kernel<")[1].split(">")[0].split(", "))
         kinds = [
             # the timed launches: causal, no counts, static power-of-two scale
-            lambda r: "_kernel<" in name(r) and ", true, false, 1," in name(r),
+            # (the KV-cache kernel's arguments are d, block, counts, scale, E4M3
+            # scores, rows, phase, ...)
+            lambda r: "_kernel<" in name(r) and ", true, false, 1," in name(r) or
+                      kv(name(r), lambda t: t[2:4] == ["false", "1"] and t[6] != "1"),
             # a split prefill's range-maxima launch and its merge
-            lambda r: "prefill_kernel<" in name(r) and name(r).split("(")[0].endswith(", 1>"),
+            lambda r: "prefill_kernel<" in name(r) and name(r).split("(")[0].endswith(", 1>") or
+                      kv(name(r), lambda t: t[6] == "1"),
             lambda r: "prefill_merge<" in name(r),
         ]
         per_call = 0.0
