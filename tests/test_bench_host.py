@@ -84,3 +84,16 @@ def test_report_markdown_and_paper_context(tmp_path):
     assert "table1_frac_zeroed=0.82" in md and "table2_mse=5.65e-05" in md
     assert bench._paper_context("C2", "reverse", 16.0, 7.0) == {}
     assert bench._paper_context("C4", "forward", 1.0, 9.0) == {}
+
+
+def test_write_traffic_kv_cache_kernel(tmp_path, monkeypatch):
+    # the KV-cache kernel: unsplit launches, or range maxima + visit + merge;
+    # its count variant is left out
+    kv = "void attn::kv_kernel<128, 128, %s, %d, false, 16, %d, 1, 8>(attn::Params)"
+    rows = [(kv % ("false", 1, 2), 100), (kv % ("true", 1, 2), 999), (kv % ("false", 0, 1), 40),
+            ("void attn::prefill_merge<128, 16>(attn::Params)", 6), ("__amd_rocclr_copyBuffer", 1024 * 1024)]
+    path = tmp_path / "c.csv"
+    monkeypatch.setattr(bench, "traffic_file", lambda w: str(tmp_path / f"traffic_{w}.json"))
+    for r, want in ((rows, 146), ([(kv % ("false", 1, 0), 70), rows[1], rows[4]], 70)):
+        _csv(path, r)
+        assert bench.write_traffic(str(path), str(path), "wl", copy_mib=1024)["fetch_kib_per_launch_raw"] == want
