@@ -38,7 +38,8 @@ def lib() -> ctypes.CDLL:
         L.probe_exp2_rate.argtypes = [I, I, P, P]
         L.probe_lds_rate.argtypes = [I, I, I, I, I, P, P, P, P]
         L.probe_coexec.argtypes = [I, I, I, I, P, P, P]
-        for f in (L.probe_cvt_range, L.probe_cvt_list, L.probe_exp2, L.probe_exp2_f64, L.probe_mfma,
+        L.probe_buffer_range.argtypes = [P, I64, I, I, I, P, P]
+        for f in (L.probe_buffer_range, L.probe_cvt_range, L.probe_cvt_list, L.probe_exp2, L.probe_exp2_f64, L.probe_mfma,
                   L.probe_mfma_fp8_scaled, L.probe_cvt_scaled_vec, L.probe_exp2_rate,
                   L.probe_lds_rate, L.probe_coexec):
             f.restype = I

@@ -16,7 +16,9 @@
 //   - how the matrix core and the vector ALU of one SIMD overlap: the matrix
 //     and the vector work of one wave and key block, each alone, split over
 //     two waves of a SIMD (the fast kernel's ping-pong) or interleaved in one
-//     wave per SIMD, and what each MFMA shape costs the vector wave.
+//     wave per SIMD, and what each MFMA shape costs the vector wave,
+//   - the range check of raw buffer loads (the K and V rows past the cache's
+//     end), to registers and straight to LDS.
 // Every kernel bounds-checks its index against n.
 #include "../../paper_2606_06521_amd/csrc/attn_common.hpp"
 
@@ -29,6 +31,24 @@ __global__ void k_exp2_f64(const float* x, int64_t n, float* out)
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n)
         out[i] = exp2_f64(x[i]);
+}
+
+// One wave loads 16 bytes per lane at base + soff + 16 lane through a buffer of
+// `records` bytes; form 1 writes them straight to LDS.
+__global__ void __launch_bounds__(64) k_buffer_range(const uint8_t* base, int records, int soff, int form, i32x4* out)
+{
+    __shared__ __attribute__((aligned(1024))) i32x4 buf[64];
+    const int lane = threadIdx.x;
+    const auto rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(base), 0, records, 0x00027000);
+    if (form == 0) {
+        out[lane] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rb, 16 * lane, soff, 0));
+        return;
+    }
+    buf[lane] = i32x4{-1, -1, -1, -1};
+    __syncthreads();
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (__attribute__((address_space(3))) void*)buf, 16, 16 * lane, soff, 0, 0);
+    __syncthreads();
+    out[lane] = buf[lane];
 }
 
 __global__ void k_cvt_range(uint32_t lo, int64_t n, uint8_t* out)
@@ -482,6 +502,17 @@ __global__ void __launch_bounds__(512) k_coexec_one(int iters, unsigned long lon
 }
 
 extern "C" {
+
+// `base` holds `bytes` bytes, all that any lane addresses; `out` 64 x 16
+int probe_buffer_range(const uint8_t* base, int64_t bytes, int records, int soff, int form, void* out, void* stream)
+{
+    if (!base || !out || records < 0 || soff < 0 || records > bytes || (int64_t)soff + 1024 > bytes || form < 0 ||
+        form > 1)
+        return -1;
+    hipLaunchKernelGGL(k_buffer_range, dim3(1), dim3(64), 0, (hipStream_t)stream, base, records, soff, form,
+                       (i32x4*)out);
+    return hipGetLastError() == hipSuccess ? 0 : -3;
+}
 
 int probe_cvt_range(uint32_t lo, int64_t n, uint8_t* out, void* stream)
 {

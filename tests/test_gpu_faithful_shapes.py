@@ -33,6 +33,24 @@ def test_shapes_against_oracle(H, nq, nk, d, block_kv):
         compare(inp, gpu, mode, S, order, causal, block_kv, label=label, scale=scale)
 
 
+@pytest.mark.parametrize("order", ["forward", "reverse"])
+def test_dynamic_scale_of_subnormal_probabilities(order):
+    # Blocks 88 to 95 nats below the running maximum: their P are FP32 subnormals
+    # (below 2^-126), cast through the convert with scales down to 2^-126; codes
+    # and counts are those of the exact product P * 2^kj.  (With the sinks last,
+    # the same blocks come before the maximum rises.)
+    for d, bkv in ((64, 64), (128, 128)):
+        inp = make_inputs(1, 2, 2, 700, d, fmt="f32", delta=91.0, seed=1790 + d)
+        dev = to_device(inp)
+        label = f"faithful dynamic delta=91 d={d} bk={bkv} {order}"
+        log(label)
+        gpu = run_gpu(dev, "faithful", 16.0, order, False, bkv, scale="dynamic")
+        compare(inp, gpu, "faithful", 16.0, order, False, bkv, label=label, scale="dynamic")
+        if order == "forward":       # neither none nor all of the other blocks' codes are zero
+            z = int(gpu[2][..., 2].sum())
+            assert 0 < z < 2 * 700 * (700 - bkv), z
+
+
 def test_exp2_is_correctly_rounded():
     # against FP64 exp2 rounded once: equal, but for values whose FP64 result lies
     # within its own error (2^-51 relative, both sides) of a rounding midpoint:

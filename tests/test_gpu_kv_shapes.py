@@ -40,6 +40,35 @@ def test_plans_against_oracle(B, Hq, Hkv, nq, nk, d, bc, mode):
         compare(inp, gpu, mode, S, order, causal, bc, label=label, scale=scale)
 
 
+@pytest.mark.parametrize("mode", ["faithful", "fast", "fp8qk"])
+@pytest.mark.parametrize("nq,nk,d,bc", [(1, 130, 64, 64), (40, 333, 128, 128), (3, 20001, 128, 64), (60, 259, 64, 128)])
+def test_rows_after_the_cache_are_not_used(nq, nk, d, bc, mode):
+    # K and V are the head of an allocation that goes on with NaN: a last block
+    # that read them (its V rows meet P = 0) would give NaN
+    fmt = {"faithful": "f32", "fast": "bf16_e4m3", "fp8qk": "e4m3"}[mode]
+    inp = last_queries(make_inputs(1, 1, 1, nk, d, fmt=fmt, delta=8.0, seed=2350 + nk), nq)
+    q, k, v = to_device(inp)
+
+    def head_of_nan(t):
+        raw = torch.full((1, 1, nk + 256, d * t.element_size()), 0x7F, dtype=torch.uint8, device="cuda")
+        if t.element_size() > 1:
+            raw = raw.view(t.dtype)
+            raw[:] = float("nan")
+        else:
+            raw = raw.view(t.dtype)
+        raw[:, :, :nk] = t
+        head = raw[:, :, :nk]
+        assert head.is_contiguous()
+        return head
+
+    dev = (q, head_of_nan(k), head_of_nan(v))
+    for S, order, causal, scale in [(256.0, "reverse", True, "static"), (16.0, "forward", False, "dynamic")]:
+        label = f"NaN after the cache {mode} nq={nq} nk={nk} d={d} bc={bc} {order} {causal}"
+        log(label)
+        gpu = run_gpu(dev, mode, S, order, causal, bc, scale=scale)
+        compare(inp, gpu, mode, S, order, causal, bc, label=label, scale=scale)
+
+
 def test_workspace_sizes():
     # Reported: room for 32 ranges per tile.  The least a call accepts is what
     # a split of 32-row tiles per query head over 8 workgroups takes, 64 x (8 x 32 + 32 d + 32)
