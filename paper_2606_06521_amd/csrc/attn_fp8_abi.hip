@@ -265,9 +265,10 @@ int launch(Call& cl, const void* q, const void* k, const void* v, float* out, fl
     }
     const float S = p.S;
     hipError_t e;
-    // the scaled convert applies 1/S exactly only for S = 2^k, and only
-    // below the E4M3 range limit (it does not saturate)
-    const bool pow2 = is_pow2_scale(S) && S <= 256.0f;
+    // the scaled convert applies 1/S exactly only for S = 2^k, only below the
+    // E4M3 range limit (it does not saturate), and only where 1/S is finite
+    // (S = 2^-128 and below: its scale operand would be infinity, every code NaN)
+    const bool pow2 = is_pow2_scale(S) && S <= 256.0f && isfinite(p.inv_S);
     const int scale = cl.dyn ? attn::kScaleDynamic : pow2 ? attn::kScalePow2 : attn::kScaleAny;
     const bool qk8 = cl.mode == ATTN_MODE_FP8QK;
     // The fast kernel's causal rows start at a block boundary: a chunk that

@@ -51,6 +51,18 @@ def test_dynamic_scale_of_subnormal_probabilities(order):
             assert 0 < z < 2 * 700 * (700 - bkv), z
 
 
+def test_scales_whose_reciprocal_overflows():
+    # S = 2^-127 is the last power of two with a finite FP32 reciprocal; below it
+    # every code is 0 too (P S < 2^-10), so the output is 0 and every key counts
+    inp = make_inputs(1, 2, 1, 150, 64, fmt="f32", delta=5.0, seed=1795)
+    dev = to_device(inp)
+    for e in (-127, -128, -149):
+        label = f"faithful S=2^{e}"
+        log(label)
+        gpu = run_gpu(dev, "faithful", 2.0 ** e, "reverse", True, 64)
+        compare(inp, gpu, "faithful", 2.0 ** e, "reverse", True, 64, label=label)
+
+
 def test_exp2_is_correctly_rounded():
     # against FP64 exp2 rounded once: equal, but for values whose FP64 result lies
     # within its own error (2^-51 relative, both sides) of a rounding midpoint:
