@@ -199,12 +199,21 @@ def _kv_workspace_bytes(device_index, *shape):
     return n
 
 
-def kv_workspace(B, Hq, Hkv, N, Nk, d, causal, block_kv, mode, device):
+def kv_workspace(B, Hq, Hkv, N, Nk, d, causal, block_kv, mode, device, stream=None):
     """A device workspace (torch-allocated) for a KV-cache call of this shape,
-    or None when the call does not split."""
+    or None when the call does not split.  stream: the stream the call runs on,
+    if not the current one; the memory belongs to it, so that torch hands it out
+    again only in that stream's order."""
     n = _kv_workspace_bytes(torch.cuda.current_device(), B, Hq, Hkv, N, Nk, d, int(bool(causal)),
                             int(block_kv), mode)
-    return torch.empty(n, dtype=torch.uint8, device=device) if n else None
+    if not n:
+        return None
+    if stream is None:
+        return torch.empty(n, dtype=torch.uint8, device=device)
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(stream.cuda_stream, device=device)
+    with torch.cuda.stream(stream):
+        return torch.empty(n, dtype=torch.uint8, device=device)
 
 
 def fwd(q, k, v, *, S: float = 256.0, order: str = "reverse", causal: bool = False,
@@ -223,7 +232,7 @@ def fwd(q, k, v, *, S: float = 256.0, order: str = "reverse", causal: bool = Fal
         out = torch.empty((B, Hq, N, d), dtype=torch.float32, device=q.device)
     if lse is None and want_lse:
         lse = torch.empty((B, Hq, N), dtype=torch.float32, device=q.device)
-    ws = kv_workspace(B, Hq, Hkv, N, Nk, d, causal, block_kv, m, q.device) if Nk != N else None
+    ws = kv_workspace(B, Hq, Hkv, N, Nk, d, causal, block_kv, m, q.device, stream) if Nk != N else None
     st = attn_fp8_fwd_kv(_ptr(q), _ptr(k), _ptr(v), _ptr(out), _ptr(lse), B, Hq, Hkv, N, Nk, d,
                          int(bool(causal)), int(block_kv), ORDERS[order], S,
                          m | SCALES[scale] | TILES[tile], *descales, _ptr(ws),
@@ -240,7 +249,7 @@ def p_underflow_count(q, k, v, *, S: float = 256.0, order: str = "reverse", caus
     m = MODES[mode]
     B, Hq, Hkv, N, d, Nk = _check(q, k, v, m)
     counts = torch.empty((B, Hq, N, 3), dtype=torch.int32, device=q.device)
-    ws = kv_workspace(B, Hq, Hkv, N, Nk, d, causal, block_kv, m, q.device) if Nk != N else None
+    ws = kv_workspace(B, Hq, Hkv, N, Nk, d, causal, block_kv, m, q.device, stream) if Nk != N else None
     st = attn_fp8_p_underflow_count_kv(_ptr(q), _ptr(k), _ptr(v), B, Hq, Hkv, N, Nk, d,
                                        int(bool(causal)), int(block_kv), ORDERS[order], S,
                                        m | SCALES[scale] | TILES[tile], int(n_sink), *descales,

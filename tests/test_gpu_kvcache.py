@@ -270,6 +270,50 @@ def test_split_workspace_two_host_threads():
         compare(probs[i], results[i], "fast", 256.0, "reverse", True, 128, label=label)
 
 
+@pytest.mark.parametrize("duck", [False, True])
+def test_workspace_belongs_to_the_call_s_stream(monkeypatch, duck):
+    # A split call on a stream that is not the current one: its workspace must not
+    # come back from torch's allocator on the current stream while the call may
+    # still run.  First with the launch replaced by a record of the pointers (a
+    # workspace of the current stream would be handed out again at once), then for
+    # real behind work that holds the side stream up.
+    import torch
+    from paper_2606_06521_amd import attn_fp8 as A
+    inp = last_queries(make_inputs(1, 8, 8, 40000, 64, fmt="bf16_e4m3", delta=8.0, seed=2410), 1)
+    q, k, v = to_device(inp)
+    side = torch.cuda.Stream()
+
+    class Handle:                        # anything with a cuda_stream is accepted
+        cuda_stream = side.cuda_stream
+
+    kw = dict(S=256.0, order="reverse", causal=True, block_kv=128, mode="fast")
+    want = A.fwd(q, k, v, **kw)
+    torch.cuda.synchronize()
+    seen = []
+    with monkeypatch.context() as m:
+        for name, at in (("attn_fp8_fwd_kv", 19), ("attn_fp8_p_underflow_count_kv", 21)):
+            m.setattr(A, name, lambda *a, at=at: seen.append((a[at], a[at + 1])) or A.ATTN_OK)
+        for call in (A.fwd, A.p_underflow_count):
+            call(q, k, v, stream=Handle() if duck else side, **kw)
+            ptr, nbytes = seen[-1]
+            assert ptr and nbytes == A.attn_fp8_kv_workspace_bytes(1, 8, 8, 1, 40000, 64, 1, 128, 1)[1]
+            again = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+            assert again.data_ptr() != ptr, call.__name__
+            del again
+    log("split call on a side stream")
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(20_000_000)
+    out = torch.empty_like(want[0])
+    lse = torch.empty_like(want[1])
+    A.fwd(q, k, v, out=out, lse=lse, stream=Handle() if duck else side, **kw)
+    junk = [torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda") for _ in range(4)]
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    assert torch.equal(out, want[0]) and torch.equal(lse, want[1])
+    del junk
+
+
 def test_workload_prefill_q256_full_size_both_schedules():
     """The KV-cache prefill workload at full size (4 x 32 query heads, 8 KV
     heads, the last 256 of 32768 positions, d = 128): 128 tiles of 256 rows
