@@ -474,11 +474,11 @@ int attn_fp8_fwd_kv_noalloc(const void* q, const void* k, const void* v, float* 
     int n_cu = 0;
     if ((st = device_cus(n_cu)) != ATTN_OK)
         return st;
-    const size_t need = workspace_min(cl, n_cu);
-    if (need > kScratchBytes)
+    if (workspace_min(cl, n_cu) > kScratchBytes)
         return ATTN_ERR_SCRATCH;
+    // the same split as with a workspace of the reported size
     void* ws = nullptr;
-    if (need > 0 && !(ws = scratch_on_device()))
+    if (workspace_bytes(cl, n_cu) > 0 && !(ws = scratch_on_device()))
         return ATTN_ERR_HIP;
     return launch(cl, q, k, v, out, lse, nullptr, nullptr, nullptr, 0, ws, ws ? kScratchBytes : 0,
                   n_cu, static_cast<hipStream_t>(stream));

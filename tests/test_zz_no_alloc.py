@@ -53,6 +53,20 @@ def test_noalloc_matches_workspace_entry_point_twice():
                     True, 128, label="noalloc vs oracle")
 
 
+def test_noalloc_splits_grouped_heads():
+    # 256 query-head tiles fill the GPU, the 8 tiles of the grouped heads do not:
+    # the call splits like the workspace entry point
+    from paper_2606_06521_amd import attn_fp8 as A
+    B, Hq, Hkv, Nq, Nk, d = 8, 32, 1, 1, 12000, 64
+    inp = last_queries(make_inputs(B, Hq, Hkv, Nk, d, fmt="bf16_e4m3", delta=8.0, seed=905), Nq)
+    log(f"noalloc grouped: B={B} Hq={Hq} Hkv={Hkv} Nq={Nq} Nk={Nk}")
+    nbytes, ((o_ws, l_ws), (o_na, l_na)) = _pair(A, inp, B, Hq, Hkv, Nq, Nk, d=d)
+    assert nbytes > 0
+    assert torch.equal(o_ws, o_na) and torch.equal(l_ws, l_na)
+    compare(inp, (o_na.cpu().numpy(), l_na.cpu().numpy(), None), "fast", 256.0, "reverse", True, 128,
+            label="noalloc grouped vs oracle")
+
+
 def test_noalloc_without_split_and_square():
     from paper_2606_06521_amd import attn_fp8 as A
     # enough tiles to fill the GPU (no split), and a square problem
