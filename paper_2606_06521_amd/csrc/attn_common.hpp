@@ -64,6 +64,7 @@ struct Params {
     int nsplit;          // workgroups per tile (1: unsplit)
     float* ws_max;       // [tile][nsplit][rows] row maxima of each range
     float* ws_part;      // [tile][nsplit][rows * d + rows] each workgroup's O sum, then l
+    int run, run_tiles;  // rows that share tiles (a group's, or one head's), and their tiles
     int causal;          // faithful and KV-cache kernels (the fast kernel takes it as a template argument)
     int row_lo;          // fast kernel: rows before this one only pad a chunk to a block boundary
 };

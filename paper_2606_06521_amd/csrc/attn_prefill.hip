@@ -32,9 +32,9 @@ __global__ void __launch_bounds__(256) prefill_merge(Params p)
         return;
     const int bk = unit / p.n_tiles;
     const int tile = p.causal ? p.n_tiles - 1 - (unit - bk * p.n_tiles) : unit - bk * p.n_tiles;   // as kv_kernel
-    const int rows = p.Hq / p.Hkv * p.N;
-    const int row = TR * tile + rr;
-    if (row >= rows)
+    const int run = tile / p.run_tiles;
+    const int row = run * p.run + TR * (tile - run * p.run_tiles) + rr;
+    if (row >= (run + 1) * p.run)
         return;
     const int piece = threadIdx.x % PIECES, part = threadIdx.x / PIECES;
     const float* base = p.ws_part + (size_t)unit * C * PART;
@@ -78,7 +78,7 @@ __global__ void __launch_bounds__(256) prefill_merge(Params p)
         m = fmax_f(m, msh[v]);
     }
     // (l and m of part 0 are the same in all its pieces)
-    const size_t flat = (size_t)bk * rows + row;
+    const size_t flat = (size_t)bk * (p.Hq / p.Hkv * p.N) + row;
     if (p.out) {
         const float inv = p.v_descale / (p.S * l);
         f32x4 v4;
@@ -109,6 +109,7 @@ struct Plan {
     int rows;              // tile height
     int cols;              // workgroups per tile that share its columns (unsplit tiles)
     int waves;             // per workgroup
+    long long run;         // rows that share tiles: a group's, or one head's (causal heads of 128 rows or more)
     long long tiles;       // per (batch, KV head)
     long long units;
     long long C;           // workgroups per tile that share its keys
@@ -146,6 +147,8 @@ Plan make_plan(const Params& p, int d, int block_kv, bool causal, bool qk8, int 
                double* time = nullptr)
 {
     const long long rows = (long long)p.Hq / p.Hkv * p.N;
+    // (fewer rows lie within 128 positions, as the rows of one block do)
+    const long long run = causal && p.N >= 128 ? p.N : rows;
     // (no tile visits more blocks than this)
     const long long nb = causal ? ((long long)p.N - 1 + p.qoff) / block_kv + 1
                                 : ((long long)p.Nk + block_kv - 1) / block_kv;
@@ -168,7 +171,8 @@ Plan make_plan(const Params& p, int d, int block_kv, bool causal, bool qk8, int 
         Plan pl{};
         pl.rows = tr;
         pl.C = 1;
-        pl.tiles = (rows + tr - 1) / tr;
+        pl.run = run;
+        pl.tiles = rows / run * ((run + tr - 1) / tr);
         pl.units = (long long)p.B * p.Hkv * pl.tiles;
         auto take = [&](double t) {
             if (best.rows == 0 || t < t_best) {
@@ -260,6 +264,8 @@ hipError_t launch_prefill(const Params& p_in, int d, int block_kv, bool causal, 
     if (slots * kNumXcd > 1 << 30)
         return hipErrorInvalidValue;
     p.n_tiles = (int)pl.tiles;
+    p.run = (int)pl.run;
+    p.run_tiles = (int)((pl.run + pl.rows - 1) / pl.rows);
     p.nsplit = (int)pl.C;
     p.total_wg = (int)(pl.units * per_unit);
     p.per_xcd = (int)slots;

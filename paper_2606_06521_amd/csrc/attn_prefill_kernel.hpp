@@ -6,7 +6,11 @@
 // The query heads of a group read the same keys, so their rows are one run of
 // G * Nq rows (contiguous in q, out, lse and counts: row R is query R % Nq of
 // head R / Nq) cut into tiles of TR = 16 or 32 rows: a decode step with four
-// query heads per KV head reads each key once instead of four times.
+// query heads per KV head reads each key once instead of four times.  Causal
+// heads of 128 rows or more get tiles of their own: every row of a tile meets
+// the V of all blocks the tile visits (with P = 0 where masked, but 0 times NaN
+// is NaN), and a tile that holds the end of one head and the start of the next
+// visits them all.  Its rows would also be masked in most of them.
 //
 // A tile's workgroup has NW = 8 or 4 waves.  They take the KV blocks of the visit
 // in rounds, wave w the block at visit position NW i + w of round i.  Each wave
@@ -193,21 +197,23 @@ __global__ void __launch_bounds__(64 * NW, 2) kv_kernel(Params p)
     // (causal: the tiles with the most blocks start first)
     const int tile = p.causal ? p.n_tiles - 1 - (unit - bk * p.n_tiles) : unit - bk * p.n_tiles;
     const int Nq = p.N, Nk = p.Nk, qoff = p.qoff;
-    const int rows = p.Hq / p.Hkv * Nq;         // query rows of the group
     const bool causal = p.causal != 0;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & (TR - 1);
     const int g = lane / TR;
-    const int row0 = TR * tile;
+    // rows of the group share tiles in runs: the whole group's, or one head's
+    const int run = tile / p.run_tiles;
+    const int rows = (run + 1) * p.run;         // end of the tile's run
+    const int row0 = run * p.run + TR * (tile - run * p.run_tiles);
     const int row = row0 + n;                   // every wave holds the same TR rows
     const int q0 = row0 % Nq;                   // the tile's first query position
     const int pos = (q0 + n) % Nq + qoff;       // the row's key position
     const int nrow = min(TR, rows - row0);
     const int pos_min = (q0 + nrow > Nq ? 0 : q0) + qoff;              // of the tile's rows
     const int pos_max = min(q0 + nrow, Nq) - 1 + qoff;
-    const size_t flat0 = (size_t)bk * rows;     // the group's first row in q, out, lse and counts
+    const size_t flat0 = (size_t)bk * (p.Hq / p.Hkv * Nq);             // the group's first row in q, out, lse and counts
     // blocks the tile visits, and this workgroup's range of them
     const int nbt = causal ? pos_max / BC + 1 : (Nk + BC - 1) / BC;
     const int it0 = PHASE == 0 ? 0 : (int)((long long)nbt * cidx / C);

@@ -69,6 +69,29 @@ def test_rows_after_the_cache_are_not_used(nq, nk, d, bc, mode):
         compare(inp, gpu, mode, S, order, causal, bc, label=label, scale=scale)
 
 
+@pytest.mark.parametrize("mode", ["fast", "fp8qk"])
+@pytest.mark.parametrize("order", ["forward", "reverse"])
+@pytest.mark.parametrize("Hq,Hkv,nq,nk,d", [(4, 1, 200, 200, 64), (6, 2, 200, 200, 128), (4, 1, 150, 350, 128)])
+def test_nan_in_v_stays_in_its_block(Hq, Hkv, nq, nk, d, order, mode):
+    # A NaN in the last key's V reaches (as 0 times NaN) rows that visit that key's
+    # block, and no row of an earlier block of positions, whichever kernel runs
+    from paper_2606_06521_amd import attn_fp8 as A
+    fmt = "e4m3" if mode == "fp8qk" else "bf16_e4m3"
+    inp = make_inputs(1, Hq, Hkv, nk, d, fmt=fmt, delta=8.0, seed=2360 + d)
+    q, k, v = to_device(last_queries(inp, nq) if nq < nk else inp)
+    bad = v.clone()
+    bad.view(torch.uint8)[:, :, nk - 1, 5] = 0x7F
+    clean = (nk - 1) // 64 * 64 - (nk - nq)            # rows before the last block of 64 positions
+    clean -= clean % 32                                # (a tile's rows lie together)
+    for tile in (None, 128, 256):
+        label = f"NaN in V {mode} Hq={Hq} nq={nq} nk={nk} d={d} {order} tile={tile}"
+        log(label)
+        kw = dict(S=256.0, order=order, causal=True, block_kv=64, mode=mode, tile=tile)
+        want = A.fwd(q, k, v, **kw)[0][:, :, :clean]
+        got = A.fwd(q, k, bad, **kw)[0][:, :, :clean]
+        assert clean >= 96 and torch.equal(got, want), label
+
+
 def test_workspace_sizes():
     # Reported: room for 32 ranges per tile.  The least a call accepts is what
     # a split of 32-row tiles per query head over 8 workgroups takes, 64 x (8 x 32 + 32 d + 32)
