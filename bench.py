@@ -44,6 +44,7 @@ KERNEL_SOURCES = ["paper_2606_06521_amd/csrc/attn_fast_kernel.hpp",
                   "paper_2606_06521_amd/csrc/attn_fast_qk8_pair.hip",
                   "paper_2606_06521_amd/csrc/attn_prefill.hip",
                   "paper_2606_06521_amd/csrc/attn_prefill_kernel.hpp",
+                  "paper_2606_06521_amd/csrc/attn_plan.hpp",
                   "paper_2606_06521_amd/csrc/attn_common.hpp"]
 HBM_PEAK_GBS = 8000.0
 # chip-wide v_exp_f32 rate measured by tests/test_gpu_probes.py::test_exp2_issue_rate

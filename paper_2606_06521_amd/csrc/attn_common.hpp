@@ -17,6 +17,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "attn_plan.hpp"
+
 namespace attn {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
@@ -73,8 +75,6 @@ struct Params {
 constexpr int kScaleAny = 0;       // static S: multiply, clamp at 448, convert
 constexpr int kScalePow2 = 1;      // static S = 2^k <= 256: the scaled convert
 constexpr int kScaleDynamic = 2;   // per-block 2^kj (S = 2^k0 its floor)
-
-constexpr int kNumXcd = 8;   // MI355X: 8 XCDs x 32 CUs, workgroup i runs on XCD i % 8
 
 // Workgroup -> (batch*head, tile).  Hardware places workgroup i on XCD i % 8;
 // the logical index gives each XCD a contiguous range, so all query tiles of

@@ -566,6 +566,4 @@ hipError_t launch_faithful(const Params& p_in, int d, int block_kv, bool causal,
                           : launch_d_bc<128, 128>(p, count, cast, scale, n_cu, stream);
 }
 
-int faithful_rows_per_wg() { return 128; }
-
 }  // namespace attn

@@ -46,7 +46,7 @@ struct Call {
     attn::Params p;
     int d, block_kv, mode;
     int tile;   // fast kernel rows per tile asked for: 256, 128 or 0 (chosen at launch)
-    bool causal, count, dyn, fast, prefill, empty;
+    bool causal, count, dyn, fast, empty;
 };
 
 // Validation of everything but the pointers, and the launch parameters.
@@ -105,13 +105,8 @@ int prepare(Call& cl, bool count, int B, int Hq, int Hkv, int N, int Nk, int d, 
     cl.count = count;
     cl.dyn = dyn;
     cl.fast = mode == ATTN_MODE_FAST || mode == ATTN_MODE_FP8QK;
-    // Queries against a longer KV cache (fast modes): short query chunks, and
-    // long ones that start inside a block, may use a workspace (the KV-cache
-    // kernel's split; which kernel runs is decided at the launch).
-    cl.prefill = cl.fast && Nk != N && (N < 128 || (Nk - N) % block_kv != 0);
-    // (the tiles a launch ends up with are counted there)
-    const int bm = cl.prefill ? attn::prefill_rows_per_wg()
-                              : cl.fast ? attn::kFastRows : attn::faithful_rows_per_wg();
+    // (a bound on the tiles; those a launch ends up with are counted there)
+    const int bm = cl.fast && !attn::kv_may_split(attn::Shape{B, Hq, Hkv, N, Nk, d, block_kv}) ? attn::kFastRows : 32;
     const int64_t n_tiles = ((int64_t)N + bm - 1) / bm;
     const int64_t total = (int64_t)B * Hq * n_tiles;
     // element offsets stay within 64-bit; the grid must fit a 1-D launch
@@ -150,18 +145,22 @@ int device_cus(int& n_cu)
     return ATTN_OK;
 }
 
+attn::Shape shape(const Call& cl)
+{
+    return {cl.p.B, cl.p.Hq, cl.p.Hkv, cl.p.N, cl.p.Nk, cl.d, cl.block_kv, cl.causal, cl.mode == ATTN_MODE_FP8QK,
+            cl.count};
+}
+
 // Workspace bytes a prepared call can use (the KV-cache split), on n_cu CUs.
 size_t workspace_bytes(const Call& cl, int n_cu)
 {
-    return cl.prefill ? attn::prefill_workspace_bytes(cl.p, cl.d, cl.block_kv, cl.causal,
-                                                      cl.mode == ATTN_MODE_FP8QK, n_cu)
-                      : 0;
+    return cl.fast ? attn::kv_workspace_bytes(shape(cl), n_cu) : 0;
 }
 
 // The least a caller's workspace has to hold (fewer ranges per tile then).
 size_t workspace_min(const Call& cl, int n_cu)
 {
-    return cl.prefill ? attn::prefill_workspace_min(cl.p, cl.d, cl.block_kv, cl.causal, n_cu) : 0;
+    return cl.fast ? attn::kv_workspace_min(shape(cl), n_cu) : 0;
 }
 
 // Validation of the pointers of a prepared, non-empty call.
@@ -183,49 +182,6 @@ int check_pointers(const Call& cl, const void* q, const void* k, const void* v, 
     if ((gap_hist || blk_zero) && (!cl.count || !gap_hist || !blk_zero || nbins < 1 || nbins > 64))
         return ATTN_ERR_INVALID_ARG;
     return ATTN_OK;
-}
-
-// Critical path of the fast kernel's persistent grid on one schedule, in
-// ping-pong phases: the largest sum of unit costs any workgroup takes, with
-// the kernel's assignment (XCD x owns units [units x / 8, units (x + 1) / 8),
-// its workgroups take every per-th of them).  A tile of the 256-row schedule
-// costs two phases per visited block (plus one block's worth for the last
-// P.V); one of the 128-row schedule one phase per block (plus two), times
-// kPairPhase, the measured length of its phases against the 256-row
-// schedule's (every phase of the 128-row schedule carries a K/V copy burst).
-constexpr double kPairPhase = 1.15;
-
-double fast_critical_path(const attn::Params& p, bool pair, int block_kv, bool causal, int n_cu)
-{
-    const int rows = pair ? attn::kFastRowsPair : attn::kFastRows;
-    const long long T = ((long long)p.N + rows - 1) / rows;
-    const long long per_head = pair ? T : (T + 1) / 2;
-    const long long units = (long long)p.B * p.Hq * per_head;
-    auto tile_cost = [&](long long t) {
-        const long long last = std::min((t + 1) * rows, (long long)p.N) - 1;
-        const long long nb = causal ? (last + p.qoff) / block_kv + 1 : ((long long)p.Nk + block_kv - 1) / block_kv;
-        return pair ? (double)(nb + 2) * kPairPhase : 2.0 * (double)(nb + 1);
-    };
-    auto unit_cost = [&](long long u) {
-        const long long pr = u % per_head;
-        if (pair)
-            return tile_cost(pr);
-        const long long a = T - 1 - pr;
-        return a == pr ? tile_cost(pr) : tile_cost(a) + tile_cost(pr);
-    };
-    const long long per_xcd_max = n_cu >= attn::kNumXcd ? n_cu / attn::kNumXcd : 1;
-    const long long per = std::min(units / attn::kNumXcd + 1, per_xcd_max);
-    double worst = 0.0;
-    for (int x = 0; x < attn::kNumXcd; ++x) {
-        const long long b = units * x / attn::kNumXcd, e = units * (x + 1) / attn::kNumXcd;
-        for (long long slot = 0; slot < per; ++slot) {
-            double sum = 0.0;
-            for (long long u = b + slot; u < e; u += per)
-                sum += unit_cost(u);
-            worst = std::max(worst, sum);
-        }
-    }
-    return worst;
 }
 
 // The fast kernel's work units: 256-row tiles in pairs, or 128-row tiles.
@@ -271,55 +227,29 @@ int launch(Call& cl, const void* q, const void* k, const void* v, float* out, fl
     const bool pow2 = is_pow2_scale(S) && S <= 256.0f && isfinite(p.inv_S);
     const int scale = cl.dyn ? attn::kScaleDynamic : pow2 ? attn::kScalePow2 : attn::kScaleAny;
     const bool qk8 = cl.mode == ATTN_MODE_FP8QK;
-    // The fast kernel's causal rows start at a block boundary: a chunk that
-    // starts inside a block is preceded by row_lo empty rows (fewer than a block).
-    attn::Params fp = p;
-    if (cl.causal) {
-        fp.row_lo = p.qoff % cl.block_kv;
-        fp.qoff = p.qoff - fp.row_lo;
-        fp.N = p.N + fp.row_lo;
-        const ptrdiff_t lo = fp.row_lo;
-        fp.q = static_cast<const uint8_t*>(p.q) - lo * cl.d * (qk8 ? 1 : 2);
-        fp.out = p.out ? p.out - lo * cl.d : nullptr;
-        fp.lse = p.lse ? p.lse - lo : nullptr;
-        fp.counts = p.counts ? p.counts - 3 * lo : nullptr;
-    }
-    set_tiles(fp, false);
-    // Kernel and schedule.  Fewer than 128 queries against a cache: the
-    // KV-cache kernel.  Otherwise 256-row tiles in causal-balanced pairs on the
-    // fast kernel, unless the caller asked otherwise or their units leave CUs
-    // idle: then the shortest, by their models, of those, the 128-row schedule
-    // (one tile per unit, two waves per 32-row group) and the KV-cache kernel.
-    // A path of the fast kernel costs 6.5 us and, per phase of a block of 128
-    // keys at d = 128, 1.3 (4096 x 4096 keys, 2 heads: 51 us for 39 phases, the
-    // KV-cache kernel 30; 512 x 512, 8 heads, causal: 17 for 7, and 10).
-    bool kv = cl.fast && p.Nk != p.N && p.N < 128;
-    bool pair = cl.tile == 128;
-    const size_t kv_ws = ws && cl.prefill ? ws_bytes : 0;
-    if (cl.fast && !kv && cl.tile == 0 && fp.units < n_cu) {
-        const double t256 = fast_critical_path(fp, false, cl.block_kv, cl.causal, n_cu);
-        const double t128 = fast_critical_path(fp, true, cl.block_kv, cl.causal, n_cu);
-        pair = t128 < t256;
-        const double phase = (0.25 + 1.05 * cl.block_kv / 128 * (cl.d == 64 ? 0.6 : qk8 ? 0.8 : 1.0)) *
-                             (cl.count ? 1.17 : 1.0);
-        kv = !gap_hist && attn::prefill_time_us(p, cl.d, cl.block_kv, cl.causal, qk8, n_cu, kv_ws) <
-                              6.5 + phase * std::min(t128, t256);
-    }
-    if (kv) {
-        e = attn::launch_prefill(p, cl.d, cl.block_kv, cl.causal, cl.count, scale, qk8, n_cu, kv_ws ? ws : nullptr,
-                                 kv_ws, s);
-    } else if (cl.fast) {
-        if (pair)
-            set_tiles(fp, true);
-        // persistent grid: one workgroup per CU (the LDS footprint admits no
-        // second one), 8 XCDs, never more workgroups than work units
-        const long long per_xcd_max = n_cu >= attn::kNumXcd ? n_cu / attn::kNumXcd : 1;
-        const long long per_xcd = fp.units / attn::kNumXcd + 1 < per_xcd_max ? fp.units / attn::kNumXcd + 1
-                                                                             : per_xcd_max;
-        const int grid = (int)(per_xcd * attn::kNumXcd);
-        auto go = [&](auto fn) { return fn(fp, grid, cl.d, cl.block_kv, cl.causal, cl.count, scale, s); };
-        e = qk8 ? (pair ? go(attn::launch_fast_t<true, true>) : go(attn::launch_fast_t<true, false>))
-                : (pair ? go(attn::launch_fast_t<false, true>) : go(attn::launch_fast_t<false, false>));
+    if (cl.fast) {
+        const attn::Route r = attn::fast_route(shape(cl), cl.tile, gap_hist != nullptr, n_cu, ws ? ws_bytes : 0);
+        if (r.kv) {
+            e = attn::launch_prefill(p, r.plan, cl.d, cl.block_kv, cl.causal, cl.count, scale, qk8, ws, s);
+        } else {
+            // row_lo empty rows in front: the pointers are those of the first of them
+            attn::Params fp = p;
+            const ptrdiff_t lo = fp.row_lo = r.row_lo;
+            fp.qoff = p.qoff - r.row_lo;
+            fp.N = p.N + r.row_lo;
+            fp.q = static_cast<const uint8_t*>(p.q) - lo * cl.d * (qk8 ? 1 : 2);
+            fp.out = p.out ? p.out - lo * cl.d : nullptr;
+            fp.lse = p.lse ? p.lse - lo : nullptr;
+            fp.counts = p.counts ? p.counts - 3 * lo : nullptr;
+            set_tiles(fp, r.pair);
+            // persistent grid: one workgroup per CU (the LDS footprint admits no
+            // second one), 8 XCDs, never more workgroups than work units
+            const long long per_xcd_max = n_cu >= attn::kNumXcd ? n_cu / attn::kNumXcd : 1;
+            const int grid = (int)(std::min(fp.units / attn::kNumXcd + 1, per_xcd_max) * attn::kNumXcd);
+            auto go = [&](auto fn) { return fn(fp, grid, cl.d, cl.block_kv, cl.causal, cl.count, scale, s); };
+            e = qk8 ? (r.pair ? go(attn::launch_fast_t<true, true>) : go(attn::launch_fast_t<true, false>))
+                    : (r.pair ? go(attn::launch_fast_t<false, true>) : go(attn::launch_fast_t<false, false>));
+        }
     } else {
         e = attn::launch_faithful(p, cl.d, cl.block_kv, cl.causal, cl.count,
                                   cl.mode == ATTN_MODE_FAITHFUL, scale, n_cu, s);
@@ -439,7 +369,7 @@ int attn_fp8_kv_workspace_bytes(int B, int Hq, int Hkv, int Nq, int Nk, int d, i
     Call cl;
     const int st = prepare(cl, false, B, Hq, Hkv, Nq, Nk, d, causal, block_kv, ATTN_ORDER_FORWARD,
                            256.0f, mode, 0, 1.0f, 1.0f, 1.0f);
-    if (st != ATTN_OK || cl.empty || !cl.prefill)
+    if (st != ATTN_OK || cl.empty || !cl.fast)
         return st;
     int n_cu = 0;
     if (device_cus(n_cu) != ATTN_OK)

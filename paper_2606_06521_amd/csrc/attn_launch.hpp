@@ -3,13 +3,13 @@
 #pragma once
 
 #include "attn_common.hpp"
+#include "attn_plan.hpp"
 
 namespace attn {
 
 // sets its own tile geometry and grid in p
 hipError_t launch_faithful(const Params& p, int d, int block_kv, bool causal, bool count,
                            bool cast, int scale, int n_cu, hipStream_t stream);
-int faithful_rows_per_wg();
 
 // The fast kernel (persistent): QK8 selects E4M3 Q and K (S^T on the FP8
 // MFMA), PAIR the 128-row schedule (two waves per 32-row group, alternate
@@ -22,20 +22,11 @@ extern template hipError_t launch_fast_t<false, false>(const Params&, int, int, 
 extern template hipError_t launch_fast_t<false, true>(const Params&, int, int, int, bool, bool, int, hipStream_t);
 extern template hipError_t launch_fast_t<true, false>(const Params&, int, int, int, bool, bool, int, hipStream_t);
 extern template hipError_t launch_fast_t<true, true>(const Params&, int, int, int, bool, bool, int, hipStream_t);
-// query rows per tile (one work unit of the 128-row schedule, half of one
-// of the 256-row schedule's tile pairs)
-constexpr int kFastRows = 256;
-constexpr int kFastRowsPair = 128;
-
-// queries against a longer KV cache (p.Nk > p.N), fast modes: one workgroup
-// per (batch, KV head, tile of the group's query rows), or several per tile when
-// the tiles cannot fill n_cu compute units (over the keys only with a
-// workspace: three launches on the stream); sets its own grid, nsplit and
-// workspace fields of p
-hipError_t launch_prefill(const Params& p, int d, int block_kv, bool causal, bool count, int scale,
-                          bool qk8, int n_cu, void* ws, size_t ws_bytes, hipStream_t stream);
-// its expected time (us), for the choice between it and the fast kernel
-double prefill_time_us(const Params& p, int d, int block_kv, bool causal, bool qk8, int n_cu, size_t ws_bytes);
+// The KV-cache kernel by its plan: one workgroup per (batch, KV head, tile of the
+// group's query rows), or several (over the keys: three launches on the stream and
+// a workspace of plan.bytes); sets its own grid, nsplit and workspace fields of p
+hipError_t launch_prefill(const Params& p, const KvPlan& plan, int d, int block_kv, bool causal, bool count,
+                          int scale, bool qk8, void* ws, hipStream_t stream);
 // One launch of the KV-cache kernel: phase 0 (unsplit), 1 (range maxima) or 2
 // (the visit per range); cols: workgroups per tile that share its columns (phase
 // 0, TR = 16); waves per workgroup: 8, or 4 (phase 0); QK8 selects E4M3 Q and K, TR the tile height.  Each
@@ -47,9 +38,5 @@ extern template hipError_t launch_kv_t<false, 16>(const Params&, int, int, bool,
 extern template hipError_t launch_kv_t<true, 16>(const Params&, int, int, bool, int, int, int, int, hipStream_t);
 extern template hipError_t launch_kv_t<false, 32>(const Params&, int, int, bool, int, int, int, int, hipStream_t);
 extern template hipError_t launch_kv_t<true, 32>(const Params&, int, int, bool, int, int, int, int, hipStream_t);
-// device workspace launch_prefill can use, and the least it accepts (0: none)
-size_t prefill_workspace_bytes(const Params& p, int d, int block_kv, bool causal, bool qk8, int n_cu);
-size_t prefill_workspace_min(const Params& p, int d, int block_kv, bool causal, int n_cu);
-int prefill_rows_per_wg();
 
 }  // namespace attn

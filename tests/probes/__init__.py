@@ -39,9 +39,20 @@ def lib() -> ctypes.CDLL:
         L.probe_lds_rate.argtypes = [I, I, I, I, I, P, P, P, P]
         L.probe_coexec.argtypes = [I, I, I, I, P, P, P]
         L.probe_buffer_range.argtypes = [P, I64, I, I, I, P, P]
-        for f in (L.probe_buffer_range, L.probe_cvt_range, L.probe_cvt_list, L.probe_exp2, L.probe_exp2_f64, L.probe_mfma,
+        L.probe_route.argtypes = [P, I, I, I, I, I, I, I, I, I64, P]
+        for f in (L.probe_route, L.probe_buffer_range, L.probe_cvt_range, L.probe_cvt_list, L.probe_exp2, L.probe_exp2_f64, L.probe_mfma,
                   L.probe_mfma_fp8_scaled, L.probe_cvt_scaled_vec, L.probe_exp2_rate,
                   L.probe_lds_rate, L.probe_coexec):
             f.restype = I
         _lib = L
     return _lib
+
+
+def route(B, Hq, Hkv, Nq, Nk, d, block_kv, causal=True, mode="fast", count=False, tile=None, diag=False,
+          n_cu=256, ws_bytes=-1) -> dict:
+    """What the library chooses for a fast-mode call (see probe_route)."""
+    bhn = (ctypes.c_int64 * 5)(B, Hq, Hkv, Nq, Nk)
+    out = (ctypes.c_int64 * 9)()
+    lib().probe_route(bhn, d, block_kv, int(causal), int(mode == "fp8qk"), int(count), tile or 0, int(diag),
+                      n_cu, ws_bytes, out)
+    return dict(zip(("kernel", "rows", "cols", "waves", "C", "units", "slots", "ws", "ws_min"), out))

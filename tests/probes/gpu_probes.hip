@@ -19,8 +19,11 @@
 //     wave per SIMD, and what each MFMA shape costs the vector wave,
 //   - the range check of raw buffer loads (the K and V rows past the cache's
 //     end), to registers and straight to LDS.
-// Every kernel bounds-checks its index against n.
+// Every kernel bounds-checks its index against n.  probe_route (host only) asks
+// the library's plan which kernel and tiling a call takes.
 #include "../../paper_2606_06521_amd/csrc/attn_common.hpp"
+
+#include <iterator>
 
 using namespace attn;
 typedef __attribute__((__vector_size__(2 * sizeof(short)))) short s16x2;
@@ -502,6 +505,23 @@ __global__ void __launch_bounds__(512) k_coexec_one(int iters, unsigned long lon
 }
 
 extern "C" {
+
+// The library's choice for a fast-mode call on n_cu compute units (host only):
+// kernel (0: KV-cache kernel, 128 or 256: the fast kernel's schedule), and the
+// KV-cache plan's rows per tile, column workgroups, waves, key ranges, units and
+// workgroups per XCD.  ws_bytes < 0: a workspace of the reported size.
+int probe_route(const int64_t* bhn, int d, int block_kv, int causal, int qk8, int count, int tile, int diag,
+                int n_cu, int64_t ws_bytes, int64_t* out)
+{
+    const Shape sh{bhn[0], bhn[1], bhn[2], bhn[3], bhn[4], d, block_kv, causal != 0, qk8 != 0, count != 0};
+    const size_t ws = ws_bytes < 0 ? kv_workspace_bytes(sh, n_cu) : (size_t)ws_bytes;
+    const Route r = fast_route(sh, tile, diag != 0, n_cu, ws);
+    const int64_t v[] = {r.kv ? 0 : r.pair ? kFastRowsPair : kFastRows, r.plan.rows, r.plan.cols, r.plan.waves,
+                         r.plan.C, r.plan.units, r.plan.slots, (int64_t)kv_workspace_bytes(sh, n_cu),
+                         (int64_t)kv_workspace_min(sh, n_cu)};
+    std::copy(std::begin(v), std::end(v), out);
+    return 0;
+}
 
 // `base` holds `bytes` bytes, all that any lane addresses; `out` 64 x 16
 int probe_buffer_range(const uint8_t* base, int64_t bytes, int records, int soff, int form, void* out, void* stream)
