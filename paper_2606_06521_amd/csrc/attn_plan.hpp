@@ -132,7 +132,7 @@ inline KvPlan kv_plan(const Shape& p, int n_cu, size_t ws_bytes)
         }
     }
     plan_bytes(best, d);
-    best.slots = (best.units + kNumXcd - 1) / kNumXcd * best.C * best.cols;
+    best.slots = (best.units * best.C * best.cols + kNumXcd - 1) / kNumXcd;
     return best;
 }
 

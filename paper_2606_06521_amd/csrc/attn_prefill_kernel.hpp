@@ -174,9 +174,10 @@ __global__ void __launch_bounds__(64 * NW, 2) kv_kernel(Params p)
     __shared__ uint32_t csh[TR][3];             // merge: counts
     __shared__ float rmax[PHASE == 2 ? 64 * NW : 1];   // PHASE 2: the maxima of every range
 
-    // workgroup -> (tile unit, range cidx of C); the C workgroups of a unit are
-    // consecutive logical indices inside one XCD's contiguous range
-    // (per_xcd is a multiple of C), so they share that XCD's L2
+    // workgroup -> (tile unit, range cidx of C).  Logical indices run over (batch,
+    // KV head), range, tile, and each XCD takes a contiguous run of per_xcd of
+    // them: the tiles that read a range's keys share an L2, and no XCD gets more
+    // workgroups than another (the ranges of a tile share nothing).
     const int C = PHASE == 0 ? 1 : p.nsplit;
     int unit, cidx;
     {
@@ -187,8 +188,11 @@ __global__ void __launch_bounds__(64 * NW, 2) kv_kernel(Params p)
         const int L = (i % kNumXcd) * p.per_xcd + slot;
         if (L >= p.total_wg)
             return;
-        unit = L / C;
-        cidx = L - unit * C;
+        const int per_range = DS * p.n_tiles;
+        const int range = L / per_range;
+        const int head = range / C;
+        cidx = range - head * C;
+        unit = head * per_range + L - range * per_range;
     }
     // DS workgroups per tile: the same scores, DO columns of V and O each
     const int colp = DS == 1 ? 0 : unit % DS;
