@@ -73,7 +73,13 @@ inline void plan_bytes(KvPlan& pl, int d)
 //   the block (777 x 777, d = 64, blocks of 64: 17 us);
 // - a (batch, KV head)'s keys come from HBM once: 40 000 per CU (decode of 16
 //   requests x 8 KV heads x 8192 keys on 128 CUs: 4.7 TB/s), 33 000 with four
-//   waves on it, 6 200 000 in all.
+//   waves on it, 6 200 000 in all.  Keys that the Infinity Cache cannot keep from
+//   call to call (96 MB and more) also cost the further reads of a range, by the
+//   tiles of its head: 75 000 per CU and a fifth of the first one's share of the
+//   total (5 x 8 heads x 32 queries x 95011 keys: 16-row tiles 300 us, 32-row
+//   ones 250).  Two workgroups that share a tile's columns go through its K at
+//   the same pace, so that each counts in full, 43 000 per CU (61 x 16384 keys on
+//   122 CUs: 124 us; split in four 104).
 // C = min(n_cu / units, blocks / 8, 512 / rows): every wave still has a block.
 inline KvPlan kv_plan(const Shape& p, int n_cu, size_t ws_bytes)
 {
@@ -85,6 +91,7 @@ inline KvPlan kv_plan(const Shape& p, int n_cu, size_t ws_bytes)
     const double k_row = p.qk8 ? d : 2 * d, v_row = d;
     const double head_keys = (double)p.B * p.Hkv * nb * block_kv;
     // one pass over `row` bytes per key on wgs workgroups of `blocks` blocks each
+    const bool cached = head_keys * (k_row + v_row) <= 96e6;
     auto pass = [&](const KvPlan& pl, double wgs, double blocks, double row) {
         const double per_cu = 8 / pl.waves, gens = ceil(wgs / (n_cu * per_cu));
         const double here = std::min(ceil(wgs / n_cu), per_cu), active = std::min(wgs, (double)n_cu);
@@ -92,8 +99,14 @@ inline KvPlan kv_plan(const Shape& p, int n_cu, size_t ws_bytes)
         const double full = maxima ? 0 : pl.rows == 32 ? 4.8 : 2.6, alone = pl.rows == 32 ? 4.0 : 3.0;
         const double round = std::max({here * pl.waves * block_kv * row / 75e3, full * here / per_cu * block_kv / 128,
                                        solo ? alone * block_kv / 128 : 0, 2.0});
-        return std::max(gens * ceil(blocks / pl.waves) * round + 4 * (gens - 1),
-                        head_keys * (maxima ? k_row : k_row + v_row) / std::min(6.2e6, (solo ? 33e3 : 40e3) * active));
+        const double once = head_keys * (maxima ? k_row : k_row + v_row), cu = solo ? 33e3 : 40e3;
+        double mem = once / std::min(6.2e6, cu * active);
+        if (!cached) {
+            const double all = std::max(once, wgs * blocks * block_kv * row), again = all - once;
+            mem = std::max((once + again / 5) / 6.2e6,
+                           (pl.cols == 2 ? all / (43e3 / 40e3 * cu) : once / cu + again / 75e3) / active);
+        }
+        return std::max(gens * ceil(blocks / pl.waves) * round + 4 * (gens - 1), mem);
     };
     KvPlan best{};
     for (int tr = 16; tr <= (rows > 16 ? 32 : 16); tr *= 2) {

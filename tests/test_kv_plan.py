@@ -18,3 +18,29 @@ def test_a_split_is_one_generation_of_workgroups(mode):
                     assert r["slots"] <= 32 and r["slots"] * 8 >= r["units"] * r["C"], (heads, nk, G, nq, r)
                     seen.add(r["units"])
     assert {1, 2, 3, 5, 9, 11, 12, 21, 33} <= seen
+
+
+@pytest.mark.parametrize("shape,mode,rows", [
+    # a cache in HBM, tiles on less than half of the compute units: by ranges of the
+    # keys (us: that, two workgroups per tile that share its columns, and the kernel
+    # of one 32-row tile per query head, which split too)
+    ((61, 1, 1, 1, 16384, 128, 128), "fast", 16),       # 104, 124, 112
+    ((64, 1, 1, 4, 16384, 128, 128), "fp8qk", 16),      # 73, 87, 78
+    ((64, 1, 1, 16, 65193, 128, 64), "fp8qk", 16),      # 274, 337, 289
+    ((61, 1, 1, 4, 65193, 64, 128), "fast", 16),        # 216, 255, 233
+    ((20, 2, 2, 1, 7503, 128, 128), "fast", 16),        # 43, 59, 47
+    ((6, 8, 8, 2, 34693, 64, 128), "fast", 16),         # 85, 130, 91
+    # two 16-row tiles of a head or one of 32 rows: the smaller ones read a range twice
+    ((5, 8, 8, 32, 95011, 128, 128), "fp8qk", 32),      # 250, 16 rows split 300, 267
+    ((7, 8, 8, 17, 7441, 128, 128), "fast", 32),        # 56, 16 rows unsplit 65, 60
+])
+def test_long_caches_are_split_where_that_is_faster(shape, mode, rows):
+    r = route(*shape, mode=mode)
+    assert r["kernel"] == 0 and r["rows"] == rows and r["C"] > 1, r
+
+
+def test_short_caches_share_the_columns():
+    # 24 x 16/2 heads x 2757 keys: 20 us by columns, 24 by ranges
+    for shape in ((24, 16, 2, 1, 2757, 128, 64), (5, 32, 8, 1, 3799, 128, 128)):
+        r = route(*shape)
+        assert r["kernel"] == 0 and r["cols"] == 2 and r["C"] == 1, r
