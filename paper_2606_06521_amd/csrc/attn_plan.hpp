@@ -145,7 +145,8 @@ inline KvPlan kv_plan(const Shape& p, int n_cu, size_t ws_bytes)
         }
     }
     plan_bytes(best, d);
-    best.slots = (best.units * best.C * best.cols + kNumXcd - 1) / kNumXcd;
+    // (the workgroups that share a tile's columns stay on one XCD)
+    best.slots = (best.units * best.C + kNumXcd - 1) / kNumXcd * best.cols;
     return best;
 }
 

@@ -41,6 +41,7 @@ def test_long_caches_are_split_where_that_is_faster(shape, mode, rows):
 
 def test_short_caches_share_the_columns():
     # 24 x 16/2 heads x 2757 keys: 20 us by columns, 24 by ranges
-    for shape in ((24, 16, 2, 1, 2757, 128, 64), (5, 32, 8, 1, 3799, 128, 128)):
+    for shape in ((24, 16, 2, 1, 2757, 128, 64), (5, 32, 8, 1, 3799, 128, 128), (3, 8, 1, 1, 4096, 128, 128)):
         r = route(*shape)
         assert r["kernel"] == 0 and r["cols"] == 2 and r["C"] == 1, r
+        assert r["slots"] % 2 == 0, r      # a pair reads the same K: one XCD
