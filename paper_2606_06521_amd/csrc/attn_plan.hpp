@@ -79,7 +79,12 @@ inline void plan_bytes(KvPlan& pl, int d)
 //   total (5 x 8 heads x 32 queries x 95011 keys: 16-row tiles 300 us, 32-row
 //   ones 250).  Two workgroups that share a tile's columns go through its K at
 //   the same pace, so that each counts in full, 43 000 per CU (61 x 16384 keys on
-//   122 CUs: 124 us; split in four 104).
+//   122 CUs: 124 us; split in four 104);
+// - the counts take about a sixth more everywhere but on 32-row tiles with bf16
+//   scores at d = 128, blocks of 128, whose kernel spills (4096 x 4096, 4 heads: 51
+//   us, with counts 75, on 16-row tiles 76 and 81; the fast kernel 51 and 62; 2048 x
+//   2048, 8 heads: 24 and 39): half more and 2 unsplit, 1.4 times split (the range
+//   maxima take no counts).
 // C = min(n_cu / units, blocks / 8, 512 / rows): every wave still has a block.
 inline KvPlan kv_plan(const Shape& p, int n_cu, size_t ws_bytes)
 {
@@ -91,6 +96,7 @@ inline KvPlan kv_plan(const Shape& p, int n_cu, size_t ws_bytes)
     const double k_row = p.qk8 ? d : 2 * d, v_row = d;
     const double head_keys = (double)p.B * p.Hkv * nb * block_kv;
     // one pass over `row` bytes per key on wgs workgroups of `blocks` blocks each
+    const bool spills = p.count && !p.qk8 && d == 128 && block_kv == 128;
     const bool cached = head_keys * (k_row + v_row) <= 96e6;
     auto pass = [&](const KvPlan& pl, double wgs, double blocks, double row) {
         const double per_cu = 8 / pl.waves, gens = ceil(wgs / (n_cu * per_cu));
@@ -117,6 +123,8 @@ inline KvPlan kv_plan(const Shape& p, int n_cu, size_t ws_bytes)
         pl.tiles = rows / run * ((run + tr - 1) / tr);
         pl.units = p.B * p.Hkv * pl.tiles;
         auto take = [&](double t) {
+            if (spills && tr == 32)
+                t = pl.C > 1 ? 1.4 * t : 1.5 * t + 2;
             if (best.rows == 0 || t < best.time_us) {
                 best = pl;
                 best.time_us = t;
@@ -169,7 +177,15 @@ inline size_t kv_workspace_min(const Shape& p, int n_cu)
 // What a call can use.
 inline size_t kv_workspace_bytes(const Shape& p, int n_cu)
 {
-    return kv_may_split(p) ? std::max(kv_workspace_min(p, n_cu), kv_plan(p, n_cu, ~(size_t)0).bytes) : 0;
+    if (!kv_may_split(p))
+        return 0;
+    size_t bytes = kv_workspace_min(p, n_cu);
+    for (const bool count : {false, true}) {   // (one size for a shape's calls with and without counts)
+        Shape s = p;
+        s.count = count;
+        bytes = std::max(bytes, kv_plan(s, n_cu, ~(size_t)0).bytes);
+    }
+    return bytes;
 }
 
 // ---- the fast kernel ----

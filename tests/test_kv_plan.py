@@ -45,3 +45,32 @@ def test_short_caches_share_the_columns():
         r = route(*shape)
         assert r["kernel"] == 0 and r["cols"] == 2 and r["C"] == 1, r
         assert r["slots"] % 2 == 0, r      # a pair reads the same K: one XCD
+
+
+@pytest.mark.parametrize("shape,causal", [
+    # (us, with counts: this plan, 32-row tiles, the kernels before)
+    ((1, 4, 4, 4096, 4096), False),      # 61, 71, 61
+    ((1, 8, 8, 2048, 2048), False),      # 38, 43, 38
+    ((1, 32, 32, 512, 512), True),       # 21, 24, 21
+    ((2, 16, 2, 286, 286), True),        # 16 or 17, 20, 17
+    ((2, 8, 8, 686, 25902), True),       # 303, 346, 303
+])
+def test_counts_avoid_the_kernel_that_spills(shape, causal):
+    r = route(*shape, 128, 128, causal=causal, count=True)
+    assert r["kernel"] == 128 or (r["kernel"] == 0 and r["rows"] == 16), r
+    # without counts, and with E4M3 scores, it is the fastest
+    assert route(*shape, 128, 128, causal=causal)["rows"] == 32
+    assert route(*shape, 128, 128, causal=causal, mode="fp8qk", count=True)["rows"] == 32
+
+
+def test_one_workspace_size_with_and_without_counts():
+    # the size query does not know which of the two calls follows
+    for nq in (1, 24, 48, 100):
+        for h in (1, 3, 7, 20):
+            for nk in (3000, 20000, 90000):
+                shape = (h, 4, 1, nq, nk, 128, 128)
+                a, b = route(*shape), route(*shape, count=True)
+                assert a["ws"] == b["ws"]
+                for r in (a, b):                       # enough for the plan either call would like most
+                    full = route(*shape, count=r is b, ws_bytes=1 << 40)
+                    assert {k: full[k] for k in full} == r, shape
