@@ -70,7 +70,9 @@ inline void plan_bytes(KvPlan& pl, int d)
 //   round of 128-key blocks takes a full CU at least 4.8 on 32-row tiles (their
 //   softmax; 2048 x 2048, 8 heads, E4M3: 31 us), 2.6 on 16-row ones, four waves
 //   alone on their CU 4.0 and 3.0 (the same 64 queries: 69 us), and 2 whatever
-//   the block (777 x 777, d = 64, blocks of 64: 17 us);
+//   the block (777 x 777, d = 64, blocks of 64: 17 us).  The long visits of a
+//   split at d = 64 show less: 3.4 on 32-row tiles, 1.5 whatever the block (13 x 4/1
+//   heads x 64 queries x 58454 E4M3 keys, blocks of 64: 144 us split, 186 unsplit);
 // - a (batch, KV head)'s keys come from HBM once: 40 000 per CU (decode of 16
 //   requests x 8 KV heads x 8192 keys on 128 CUs: 4.7 TB/s), 33 000 with four
 //   waves on it, 6 200 000 in all.  Keys that the Infinity Cache cannot keep from
@@ -102,9 +104,10 @@ inline KvPlan kv_plan(const Shape& p, int n_cu, size_t ws_bytes)
         const double per_cu = 8 / pl.waves, gens = ceil(wgs / (n_cu * per_cu));
         const double here = std::min(ceil(wgs / n_cu), per_cu), active = std::min(wgs, (double)n_cu);
         const bool maxima = row == k_row, solo = here < per_cu;
-        const double full = maxima ? 0 : pl.rows == 32 ? 4.8 : 2.6, alone = pl.rows == 32 ? 4.0 : 3.0;
+        const double small = d == 64 && pl.C > 1 ? 0.7 : 1;
+        const double full = maxima ? 0 : pl.rows == 32 ? 4.8 * small : 2.6, alone = pl.rows == 32 ? 4.0 : 3.0;
         const double round = std::max({here * pl.waves * block_kv * row / 75e3, full * here / per_cu * block_kv / 128,
-                                       solo ? alone * block_kv / 128 : 0, 2.0});
+                                       solo ? alone * block_kv / 128 : 0, small < 1 ? 1.5 : 2.0});
         const double once = head_keys * (maxima ? k_row : k_row + v_row), cu = solo ? 33e3 : 40e3;
         double mem = once / std::min(6.2e6, cu * active);
         if (!cached) {

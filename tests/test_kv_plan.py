@@ -30,6 +30,7 @@ def test_a_split_is_one_generation_of_workgroups(mode):
     ((61, 1, 1, 4, 65193, 64, 128), "fast", 16),        # 216, 255, 233
     ((20, 2, 2, 1, 7503, 128, 128), "fast", 16),        # 43, 59, 47
     ((6, 8, 8, 2, 34693, 64, 128), "fast", 16),         # 85, 130, 91
+    ((13, 4, 1, 64, 58454, 64, 64), "fp8qk", 32),       # 144, 16 rows unsplit 186, 125
     # two 16-row tiles of a head or one of 32 rows: the smaller ones read a range twice
     ((5, 8, 8, 32, 95011, 128, 128), "fp8qk", 32),      # 250, 16 rows split 300, 267
     ((7, 8, 8, 17, 7441, 128, 128), "fast", 32),        # 56, 16 rows unsplit 65, 60
