@@ -72,7 +72,9 @@ inline void plan_bytes(KvPlan& pl, int d)
 //   alone on their CU 4.0 and 3.0 (the same 64 queries: 69 us), and 2 whatever
 //   the block (777 x 777, d = 64, blocks of 64: 17 us).  The long visits of a
 //   split at d = 64 show less: 3.4 on 32-row tiles, 1.5 whatever the block (13 x 4/1
-//   heads x 64 queries x 58454 E4M3 keys, blocks of 64: 144 us split, 186 unsplit);
+//   heads x 64 queries x 58454 E4M3 keys, blocks of 64: 144 us split, 186 unsplit),
+//   and so do two workgroups of four waves with E4M3 scores (16/4 heads x 1995
+//   queries x 3914 keys: 37 us, the fast kernel 63);
 // - a (batch, KV head)'s keys come from HBM once: 40 000 per CU (decode of 16
 //   requests x 8 KV heads x 8192 keys on 128 CUs: 4.7 TB/s), 33 000 with four
 //   waves on it, 6 200 000 in all.  Keys that the Infinity Cache cannot keep from
@@ -104,7 +106,7 @@ inline KvPlan kv_plan(const Shape& p, int n_cu, size_t ws_bytes)
         const double per_cu = 8 / pl.waves, gens = ceil(wgs / (n_cu * per_cu));
         const double here = std::min(ceil(wgs / n_cu), per_cu), active = std::min(wgs, (double)n_cu);
         const bool maxima = row == k_row, solo = here < per_cu;
-        const double small = d == 64 && pl.C > 1 ? 0.7 : 1;
+        const double small = d == 64 && (pl.C > 1 || (pl.rows == 32 && pl.waves == 4 && p.qk8)) ? 0.7 : 1;
         const double full = maxima ? 0 : pl.rows == 32 ? 4.8 * small : 2.6, alone = pl.rows == 32 ? 4.0 : 3.0;
         const double round = std::max({here * pl.waves * block_kv * row / 75e3, full * here / per_cu * block_kv / 128,
                                        solo ? alone * block_kv / 128 : 0, small < 1 ? 1.5 : 2.0});
