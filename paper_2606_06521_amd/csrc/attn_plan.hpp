@@ -35,6 +35,13 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 constexpr int kMaxRanges = 512;   // nsplit * tile height (range maxima staged by one workgroup)
 
+// Two workgroups per tile that share its columns: where no shape makes them the
+// shortest (d = 64 and small blocks leave each too little), they are not built.
+constexpr bool kv_cols_built(int d, int block_kv, bool qk8, int waves)
+{
+    return d == 128 ? waves == 8 || !qk8 || block_kv == 128 : waves == 8 && !(qk8 && block_kv == 64);
+}
+
 struct KvPlan {
     int rows;              // tile height
     int cols;              // workgroups per tile that share its columns (unsplit tiles)
@@ -139,7 +146,7 @@ inline KvPlan kv_plan(const Shape& p, int n_cu, size_t ws_bytes)
             const double launch = pl.waves == 8 ? 7 : 5;
             pl.cols = 1;
             take(launch + pass(pl, (double)pl.units, (double)nb, k_row + v_row));
-            if (tr == 16 && 2 * pl.units <= n_cu) {
+            if (tr == 16 && 2 * pl.units <= n_cu && kv_cols_built(d, block_kv, p.qk8, pl.waves)) {
                 pl.cols = 2;
                 take(launch + pass(pl, 2.0 * pl.units, (double)nb, k_row + v_row / 2));
             }

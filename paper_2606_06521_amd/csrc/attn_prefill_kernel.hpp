@@ -719,9 +719,16 @@ hipError_t kv_launch(const Params& p, int scale, int phase, int cols, int waves,
         return go(kv_kernel<D, BC, false, kScaleAny, QK8, TR, 1, 1, 8>);
     if (phase == 2)
         return by_scale(two, one, w8);
-    if constexpr (TR == 16) {
-        if (cols == 2)
-            return waves == 4 ? by_scale(unsplit, two, w4) : by_scale(unsplit, two, w8);
+    if (cols == 2) {
+        if constexpr (TR == 16 && kv_cols_built(D, BC, QK8, 8)) {
+            if (waves == 8)
+                return by_scale(unsplit, two, w8);
+        }
+        if constexpr (TR == 16 && kv_cols_built(D, BC, QK8, 4)) {
+            if (waves == 4)
+                return by_scale(unsplit, two, w4);
+        }
+        return hipErrorInvalidValue;   // (no plan asks for it)
     }
     return waves == 4 ? by_scale(unsplit, one, w4) : by_scale(unsplit, one, w8);
 }

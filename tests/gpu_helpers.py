@@ -40,6 +40,27 @@ def to_device(inp):
     return q, k, v
 
 
+def device_cus() -> int:
+    return torch.cuda.get_device_properties(torch.cuda.current_device()).multi_processor_count
+
+
+def plan_of(mode, d, block_kv, shape, causal=True, count=False, n_cu=256, ws_bytes=-1):
+    """(rows per tile, plan) of a call (B, Hq, Hkv, Nq, Nk) on the KV-cache kernel:
+    "split" over ranges of its keys, or "c<workgroups per tile>w<waves>"; None if it
+    takes the fast kernel."""
+    from tests.probes import route
+    r = route(*shape, d, block_kv, causal, mode, count=count, n_cu=n_cu, ws_bytes=ws_bytes)
+    if r["kernel"] != 0:
+        return None
+    return r["rows"], "split" if r["C"] > 1 else f"c{r['cols']}w{r['waves']}"
+
+
+def assert_splits(mode, d, block_kv, shape, causal=True, count=False) -> None:
+    """The call is split over ranges of its keys on this device."""
+    p = plan_of(mode, d, block_kv, shape, causal, count, device_cus())
+    assert p is not None and p[1] == "split", (mode, d, block_kv, shape, p)
+
+
 def run_gpu(dev, mode, S, order, causal, block_kv, n_sink=4, counts=True, scale="static",
             descales=(1.0, 1.0, 1.0), tile=None):
     from paper_2606_06521_amd import attn_fp8 as A

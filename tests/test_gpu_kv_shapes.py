@@ -1,5 +1,5 @@
 """The KV-cache kernel's plans (16- or 32-row tiles of a group's query rows, four
-or eight waves, unsplit, by columns, or over ranges of the keys), each at lengths that leave
+or eight waves, unsplit, by columns, or over ranges of the keys) at lengths that leave
 partial tiles, partial last blocks, rounds with idle waves and tiles that hold
 rows of several query heads, against the oracle on every row; and workspaces
 between the least and the reported size."""
@@ -8,33 +8,114 @@ import pytest
 import torch
 
 from paper_2606_06521_amd.inputs import last_queries, make_inputs
-from tests.gpu_helpers import compare, log, run_gpu, to_device
+from tests.gpu_helpers import compare, device_cus, log, plan_of, run_gpu, to_device
 
 pytestmark = pytest.mark.gpu
 
-# (B, Hq, Hkv, Nq, Nk, d, block_kv): the plan on 256 compute units
+# (B, Hq, Hkv, Nq, Nk, d, block_kv)
 SHAPES = [
-    (1, 8, 2, 1, 20000, 128, 128),     # 16 rows, 19 ranges of the keys
-    (1, 8, 8, 3, 515, 64, 64),         # 16 rows, eight waves
-    (2, 16, 4, 8, 1501, 128, 64),      # 16 rows, two workgroups by columns, rows of two heads per tile
-    (1, 8, 4, 8, 200, 128, 64),        # 16 rows, four waves, by columns
-    (60, 8, 4, 4, 333, 64, 128),       # 16 rows, four waves
-    (40, 8, 8, 37, 261, 64, 64),       # the same in two generations
-    (16, 8, 8, 33, 1300, 128, 128),    # 32 rows, four waves
-    (16, 8, 8, 60, 2600, 128, 128),    # 32 rows, eight waves
-    (1, 16, 1, 120, 12001, 128, 128),  # 32 rows, 4 ranges, rows of up to two heads per tile
+    (1, 8, 2, 1, 20000, 128, 128),
+    (1, 8, 8, 3, 515, 64, 64),
+    (2, 16, 4, 8, 1501, 128, 64),      # rows of two heads per tile
+    (1, 8, 4, 8, 200, 128, 64),
+    (60, 8, 4, 4, 333, 64, 128),
+    (40, 8, 8, 37, 261, 64, 64),
+    (16, 8, 8, 33, 1300, 128, 128),
+    (16, 8, 8, 60, 2600, 128, 128),
+    (1, 16, 1, 120, 12001, 128, 128),  # rows of up to two heads per tile
+]
+
+# Every instantiation of the kernel: mode, d, block_kv, rows per tile, plan on 256
+# compute units ("c2w4": unsplit, two workgroups per tile, four waves each; "split":
+# ranges of the keys), and a shape (B, Hq, Hkv, Nq, Nk) that takes it with and
+# without counts (tests/test_kv_plan.py checks that), with a partial last tile, a
+# partial last block and more than one round of the waves.
+INSTANCES = [
+    ("fast", 128, 128, 16, "c1w4", (2, 1, 1, 17, 517)),
+    ("fast", 128, 128, 16, "c1w8", (3, 9, 3, 77, 2566)),
+    ("fast", 128, 128, 16, "c2w4", (2, 1, 1, 1, 538)),
+    ("fast", 128, 128, 16, "c2w8", (2, 1, 1, 1, 1560)),
+    ("fast", 128, 128, 16, "split", (2, 1, 1, 2, 5059)),
+    ("fast", 128, 128, 32, "c1w4", (12, 16, 1, 45, 515)),
+    ("fast", 128, 128, 32, "c1w8", (8, 16, 1, 33, 2628)),
+    ("fast", 128, 128, 32, "split", (1, 32, 2, 33, 7082)),
+    ("fast", 128, 64, 16, "c1w4", (1, 2, 2, 1, 263)),
+    ("fast", 128, 64, 16, "c1w8", (2, 24, 3, 45, 784)),
+    ("fast", 128, 64, 16, "c2w4", (2, 1, 1, 1, 329)),
+    ("fast", 128, 64, 16, "c2w8", (1, 2, 2, 1, 772)),
+    ("fast", 128, 64, 16, "split", (1, 2, 2, 1, 3549)),
+    ("fast", 128, 64, 32, "c1w4", (3, 32, 2, 45, 263)),
+    ("fast", 128, 64, 32, "c1w8", (2, 48, 3, 45, 801)),
+    ("fast", 128, 64, 32, "split", (1, 16, 2, 45, 3009)),
+    ("fast", 64, 128, 16, "c1w4", (3, 12, 4, 120, 531)),
+    ("fast", 64, 128, 16, "c1w8", (3, 16, 2, 45, 1033)),
+    ("fast", 64, 128, 16, "c2w8", (2, 1, 1, 1, 1031)),
+    ("fast", 64, 128, 16, "split", (1, 2, 2, 1, 6195)),
+    ("fast", 64, 128, 32, "c1w4", (12, 16, 1, 45, 525)),
+    ("fast", 64, 128, 32, "c1w8", (2, 48, 3, 45, 4659)),
+    ("fast", 64, 128, 32, "split", (1, 8, 2, 45, 11198)),
+    ("fast", 64, 64, 16, "c1w4", (3, 12, 4, 120, 258)),
+    ("fast", 64, 64, 16, "c1w8", (1, 2, 2, 1, 532)),
+    ("fast", 64, 64, 16, "c2w8", (1, 2, 2, 1, 833)),
+    ("fast", 64, 64, 16, "split", (2, 1, 1, 1, 3686)),
+    ("fast", 64, 64, 32, "c1w4", (3, 64, 4, 45, 259)),
+    ("fast", 64, 64, 32, "c1w8", (8, 16, 1, 33, 776)),
+    ("fast", 64, 64, 32, "split", (3, 3, 1, 77, 3061)),
+    ("fp8qk", 128, 128, 16, "c1w4", (40, 4, 4, 2, 525)),
+    ("fp8qk", 128, 128, 16, "c1w8", (3, 16, 2, 45, 1058)),
+    ("fp8qk", 128, 128, 16, "c2w4", (40, 3, 3, 1, 775)),
+    ("fp8qk", 128, 128, 16, "c2w8", (2, 1, 1, 1, 1039)),
+    ("fp8qk", 128, 128, 16, "split", (2, 1, 1, 2, 6024)),
+    ("fp8qk", 128, 128, 32, "c1w4", (40, 16, 1, 13, 513)),
+    ("fp8qk", 128, 128, 32, "c1w8", (2, 64, 4, 33, 1573)),
+    ("fp8qk", 128, 128, 32, "split", (2, 4, 1, 45, 11203)),
+    ("fp8qk", 128, 64, 16, "c1w4", (8, 16, 2, 33, 258)),
+    ("fp8qk", 128, 64, 16, "c1w8", (1, 2, 2, 1, 530)),
+    ("fp8qk", 128, 64, 16, "c2w8", (2, 1, 1, 1, 596)),
+    ("fp8qk", 128, 64, 16, "split", (2, 1, 1, 3, 3527)),
+    ("fp8qk", 128, 64, 32, "c1w4", (3, 64, 4, 45, 261)),
+    ("fp8qk", 128, 64, 32, "c1w8", (2, 64, 4, 33, 771)),
+    ("fp8qk", 128, 64, 32, "split", (1, 6, 2, 100, 3521)),
+    ("fp8qk", 64, 128, 16, "c1w4", (12, 8, 1, 45, 515)),
+    ("fp8qk", 64, 128, 16, "c1w8", (2, 1, 1, 1, 1037)),
+    ("fp8qk", 64, 128, 16, "c2w8", (2, 3, 1, 1, 1573)),
+    ("fp8qk", 64, 128, 16, "split", (2, 1, 1, 1, 5086)),
+    ("fp8qk", 64, 128, 32, "c1w4", (20, 4, 2, 100, 518)),
+    ("fp8qk", 64, 128, 32, "c1w8", (3, 32, 2, 45, 5735)),
+    ("fp8qk", 64, 128, 32, "split", (1, 6, 2, 60, 11141)),
+    ("fp8qk", 64, 64, 16, "c1w4", (3, 32, 4, 45, 258)),
+    ("fp8qk", 64, 64, 16, "c1w8", (2, 2, 1, 1, 521)),
+    ("fp8qk", 64, 64, 16, "split", (1, 2, 2, 2, 3041)),
+    ("fp8qk", 64, 64, 32, "c1w4", (5, 16, 4, 100, 267)),
+    ("fp8qk", 64, 64, 32, "c1w8", (8, 16, 1, 33, 797)),
+    ("fp8qk", 64, 64, 32, "split", (2, 3, 1, 100, 3521)),
 ]
 
 
 @pytest.mark.parametrize("mode", ["fast", "fp8qk"])
 @pytest.mark.parametrize("B,Hq,Hkv,nq,nk,d,bc", SHAPES)
-def test_plans_against_oracle(B, Hq, Hkv, nq, nk, d, bc, mode):
+def test_shapes_against_oracle(B, Hq, Hkv, nq, nk, d, bc, mode):
     fmt = "e4m3" if mode == "fp8qk" else "bf16_e4m3"
     inp = last_queries(make_inputs(B, Hq, Hkv, nk, d, fmt=fmt, delta=8.0, seed=2300 + nk), nq)
     dev = to_device(inp)
     for S, order, causal, scale in [(256.0, "reverse", True, "static"), (16.0, "forward", False, "dynamic"),
                                     (3.0, "forward", True, "static")]:
         label = f"kv plan {mode} B={B} Hq={Hq} Hkv={Hkv} nq={nq} nk={nk} d={d} bc={bc} S={S} {order} {causal}"
+        log(label)
+        gpu = run_gpu(dev, mode, S, order, causal, bc, scale=scale)
+        compare(inp, gpu, mode, S, order, causal, bc, label=label, scale=scale)
+
+
+@pytest.mark.parametrize("mode,d,bc,rows,plan,shape", INSTANCES, ids=lambda x: str(x).replace(" ", ""))
+def test_instances_against_oracle(mode, d, bc, rows, plan, shape):
+    B, Hq, Hkv, nq, nk = shape
+    assert plan_of(mode, d, bc, shape, n_cu=device_cus()) == (rows, plan)
+    fmt = "e4m3" if mode == "fp8qk" else "bf16_e4m3"
+    inp = last_queries(make_inputs(B, Hq, Hkv, nk, d, fmt=fmt, delta=8.0, seed=2700 + nk), nq)
+    dev = to_device(inp)
+    for S, order, causal, scale in [(256.0, "reverse", True, "static"), (16.0, "forward", False, "dynamic"),
+                                    (3.0, "reverse", True, "static")]:
+        label = f"kv {rows} rows {plan} {mode} d={d} bc={bc} {shape} S={S} {order} {causal}"
         log(label)
         gpu = run_gpu(dev, mode, S, order, causal, bc, scale=scale)
         compare(inp, gpu, mode, S, order, causal, bc, label=label, scale=scale)

@@ -1,8 +1,33 @@
 """The library's kernel choice and KV-cache plan (host code, asked through the
 probe library; no GPU needed), on 256 compute units unless said otherwise."""
+import itertools
+
 import pytest
 
+from tests.gpu_helpers import plan_of
 from tests.probes import route
+from tests.test_gpu_kv_shapes import INSTANCES
+
+
+def test_instances_take_the_plan_they_name():
+    # the GPU test of the kernel's instantiations runs each with and without counts
+    for mode, d, bc, rows, plan, shape in INSTANCES:
+        B, Hq, Hkv, nq, nk = shape
+        assert nk % bc != 0 and (Hq // Hkv * nq) % rows != 0 and nq < 128
+        for causal, count in itertools.product((True, False), (True, False)):
+            assert plan_of(mode, d, bc, shape, causal, count) == (rows, plan), (mode, d, bc, shape)
+
+
+def test_instances_are_all_there_are():
+    # per mode, d and block: 16-row tiles unsplit on eight and four waves, or split;
+    # the same for 32-row ones; and the column pairs that are built
+    want = {(m, d, bc, rows, plan) for m, d, bc in itertools.product(("fast", "fp8qk"), (64, 128), (64, 128))
+            for rows, plan in itertools.product((16, 32), ("c1w8", "c1w4", "split"))}
+    want |= {("fast", 64, 64, 16, "c2w8"), ("fast", 64, 128, 16, "c2w8"), ("fast", 128, 64, 16, "c2w8"),
+             ("fast", 128, 64, 16, "c2w4"), ("fast", 128, 128, 16, "c2w8"), ("fast", 128, 128, 16, "c2w4"),
+             ("fp8qk", 64, 128, 16, "c2w8"), ("fp8qk", 128, 64, 16, "c2w8"), ("fp8qk", 128, 128, 16, "c2w8"),
+             ("fp8qk", 128, 128, 16, "c2w4")}
+    assert {i[:5] for i in INSTANCES} == want and len(INSTANCES) == len(want)
 
 
 @pytest.mark.parametrize("mode", ["fast", "fp8qk"])
