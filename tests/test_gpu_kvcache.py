@@ -1,5 +1,5 @@
 """Queries against a KV cache (Nq < Nk) on the device against the oracle:
-the prefill kernel (fast modes) and the faithful kernel with a query offset.
+the KV-cache kernel (fast modes) and the faithful kernel with a query offset.
 Same bar as the square problems: counts exact where claimed, outputs within
 the mode's tolerance (plus the code-ambiguity bound in the fast modes), lse
 within 1e-4."""
@@ -10,7 +10,7 @@ import pytest
 
 from paper_2606_06521_amd.inputs import last_queries, make_inputs
 from paper_2606_06521_amd.workloads import WORKLOADS
-from tests.gpu_helpers import compare, log, run_gpu, to_device
+from tests.gpu_helpers import assert_splits, compare, device_cus, log, run_gpu, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -37,9 +37,8 @@ def test_small(mode, d, bkv):
 @pytest.mark.parametrize("mode", ["fast", "fp8qk"])
 @pytest.mark.parametrize("bkv", [64, 128])
 def test_long_chunks(mode, bkv, tile):
-    # 256 queries with a block-aligned offset (Nk = 640) take the persistent
-    # kernel (on either schedule); 200 queries at offset 133 (Nk = 333) the
-    # prefill kernel (where the schedule flag has no effect)
+    # 256 queries with a block-aligned offset (Nk = 640), and 200 at offset 133,
+    # inside a block (Nk = 333): the persistent kernel, on either schedule
     for nk, nq in ((640, 256), (333, 200)):
         full = make_inputs(1, 4, 2, nk, 128, fmt=FMT[mode], delta=9.0, seed=960 + nk + bkv)
         inp = last_queries(full, nq)
@@ -54,14 +53,14 @@ def test_long_chunks(mode, bkv, tile):
 
 
 @pytest.mark.parametrize("mode", ["fast", "fp8qk"])
-@pytest.mark.parametrize("d,bkv,nk", [(128, 128, 2000), (64, 64, 4500), (128, 64, 1100), (64, 128, 3000)])
+@pytest.mark.parametrize("d,bkv,nk", [(128, 128, 7500), (64, 64, 4500), (128, 64, 5100), (64, 128, 6900)])
 def test_split_over_workgroups(mode, d, bkv, nk):
-    # Few 32-row tiles against many KV blocks: the prefill kernel splits each
-    # tile's visit order over C = min(CUs / tiles, blocks / 8, 8) workgroups
-    # (on 256 CUs: C = 2, 8, 2 and 3 for these caches), two launches and a
-    # cross-workgroup merge.  Ragged caches, one row and a ragged 45-row chunk.
+    # Few tiles against many KV blocks: the KV-cache kernel splits each tile's
+    # visit into C ranges, one workgroup each (range maxima, the visit, a merge).
+    # Ragged caches, one row and a ragged 45-row chunk.
     full = make_inputs(1, 2, 1, nk, d, fmt=FMT[mode], delta=9.0, seed=970 + d + bkv + nk)
     for nq in (1, 45):
+        assert_splits(mode, d, bkv, (1, 2, 1, nq, nk))
         inp = last_queries(full, nq)
         dev = to_device(inp)
         for (causal, order), (S, scale) in itertools.product(
@@ -75,9 +74,9 @@ def test_split_over_workgroups(mode, d, bkv, nk):
 
 @pytest.mark.parametrize("mode", ["fast", "fp8qk"])
 def test_split_over_workgroups_gqa(mode):
-    # GQA 8:1 with two batches: 2 * 8 * 2 = 32 tiles of 32 rows against 2500
-    # keys (20 blocks of 128): C = min(256 / 32, 20 / 8, 8) = 2 workgroups per tile
-    full = make_inputs(2, 8, 1, 2500, 128, fmt=FMT[mode], delta=9.0, seed=990)
+    # GQA 8:1 with two batches: the 400 query rows of a group in shared tiles
+    full = make_inputs(2, 8, 1, 7250, 128, fmt=FMT[mode], delta=9.0, seed=990)
+    assert_splits(mode, 128, 128, (2, 8, 1, 50, 7250))
     inp = last_queries(full, 50)
     dev = to_device(inp)
     for causal, order in itertools.product([False, True], ["forward", "reverse"]):
@@ -88,8 +87,9 @@ def test_split_over_workgroups_gqa(mode):
 
 
 def test_split_over_workgroups_descaled():
-    # a split tile (C = 4) with per-tensor descales on E4M3 Q, K and V
-    full = make_inputs(1, 2, 1, 4096, 128, fmt="e4m3", delta=8.0, seed=985)
+    # a split tile with per-tensor descales on E4M3 Q, K and V
+    full = make_inputs(1, 2, 1, 7300, 128, fmt="e4m3", delta=8.0, seed=985)
+    assert_splits("fp8qk", 128, 128, (1, 2, 1, 32, 7300))
     inp = last_queries(full, 32)
     dev = to_device(inp)
     ds = (0.75, 1.5, 2.0)
@@ -161,9 +161,13 @@ def test_split_workspace_is_the_callers():
     # equal the oracle, codes and counts included.
     import torch
     from paper_2606_06521_amd import attn_fp8 as A
-    inp = last_queries(make_inputs(2, 4, 2, 3000, 128, fmt="bf16_e4m3", delta=8.0, seed=995), 20)
+    from tests.probes import route
+    B, Hq, Hkv, Nq, Nk, d = 2, 4, 2, 20, 5300, 128
+    inp = last_queries(make_inputs(B, Hq, Hkv, Nk, d, fmt="bf16_e4m3", delta=8.0, seed=995), Nq)
     q, k, v = to_device(inp)
-    B, Hq, Hkv, Nq, Nk, d = 2, 4, 2, 20, 3000, 128
+    for count in (False, True):
+        assert_splits("fast", d, 128, (B, Hq, Hkv, Nq, Nk), count=count)
+    least = route(B, Hq, Hkv, Nq, Nk, d, 128, n_cu=device_cus())["ws_min"]
     st, nbytes = A.attn_fp8_kv_workspace_bytes(B, Hq, Hkv, Nq, Nk, d, 1, 128, A.ATTN_MODE_FAST)
     assert st == 0 and nbytes > 0
     # square problems and the faithful mode never split
@@ -179,6 +183,10 @@ def test_split_workspace_is_the_callers():
                                B, Hq, Hkv, Nq, Nk, d, 1, 128, 1, 256.0, 1, 1.0, 1.0, 1.0, wptr,
                                wbytes, sptr)
         assert st == 0, label
+        if wptr:                                  # the call did split: the maxima of its ranges
+            torch.cuda.synchronize()
+            assert not torch.isnan(ws[:256].view(torch.float32)).any()
+            ws.fill_(0xFF)
         st = A.attn_fp8_p_underflow_count_kv(q.data_ptr(), k.data_ptr(), v.data_ptr(), B, Hq, Hkv,
                                              Nq, Nk, d, 1, 128, 1, 256.0, 1, 4, 1.0, 1.0, 1.0,
                                              c.data_ptr(), None, None, wptr, wbytes, sptr)
@@ -189,8 +197,8 @@ def test_split_workspace_is_the_callers():
                 256.0, "reverse", True, 128, label=label)
     st = A.attn_fp8_fwd_kv(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), None, B, Hq,
                            Hkv, Nq, Nk, d, 1, 128, 1, 256.0, 1, 1.0, 1.0, 1.0, ws.data_ptr(),
-                           nbytes - 1, sptr)
-    assert st == A.ATTN_ERR_INVALID_ARG
+                           least - 1, sptr)
+    assert 0 < least <= nbytes and st == A.ATTN_ERR_INVALID_ARG
     st = A.attn_fp8_fwd_kv(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), None, B, Hq,
                            Hkv, Nq, Nk, d, 1, 128, 1, 256.0, 1, 1.0, 1.0, 1.0,
                            ws.data_ptr() + 16, nbytes - 16, sptr)
@@ -204,7 +212,8 @@ def test_split_call_in_a_captured_graph():
     # bit for bit, and that result equals the oracle.
     import torch
     from paper_2606_06521_amd import attn_fp8 as A
-    inp = last_queries(make_inputs(1, 8, 2, 2600, 128, fmt="bf16_e4m3", delta=8.0, seed=981), 24)
+    inp = last_queries(make_inputs(1, 8, 2, 5300, 128, fmt="bf16_e4m3", delta=8.0, seed=981), 24)
+    assert_splits("fast", 128, 128, (1, 8, 2, 24, 5300))
     q, k, v = to_device(inp)
     o_eager, l_eager = A.fwd(q, k, v, S=256.0, order="reverse", causal=True, block_kv=128,
                              mode="fast")
@@ -239,8 +248,10 @@ def test_split_workspace_two_host_threads():
     import threading
     import torch
     from paper_2606_06521_amd import attn_fp8 as A
-    probs = [last_queries(make_inputs(1, 2, 1, 2500, 128, fmt="bf16_e4m3", delta=8.0, seed=997), 24),
-             last_queries(make_inputs(2, 4, 2, 3000, 128, fmt="bf16_e4m3", delta=9.0, seed=998), 33)]
+    probs = [last_queries(make_inputs(1, 2, 1, 5300, 128, fmt="bf16_e4m3", delta=8.0, seed=997), 24),
+             last_queries(make_inputs(2, 4, 2, 5500, 128, fmt="bf16_e4m3", delta=9.0, seed=998), 33)]
+    for shape in ((1, 2, 1, 24, 5300), (2, 4, 2, 33, 5500)):
+        assert_splits("fast", 128, 128, shape)
     devs = [to_device(p) for p in probs]
     results = [None, None]
     errors = []
@@ -280,6 +291,7 @@ def test_workspace_belongs_to_the_call_s_stream(monkeypatch, duck):
     import torch
     from paper_2606_06521_amd import attn_fp8 as A
     inp = last_queries(make_inputs(1, 8, 8, 40000, 64, fmt="bf16_e4m3", delta=8.0, seed=2410), 1)
+    assert_splits("fast", 64, 128, (1, 8, 8, 1, 40000))
     q, k, v = to_device(inp)
     side = torch.cuda.Stream()
 

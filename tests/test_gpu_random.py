@@ -8,7 +8,7 @@ import numpy as np
 import pytest
 
 from paper_2606_06521_amd.inputs import last_queries, make_inputs
-from tests.gpu_helpers import compare, log, run_gpu, to_device
+from tests.gpu_helpers import assert_splits, compare, log, plan_of, run_gpu, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -56,16 +56,22 @@ def test_random_config(seed):
 
 
 def _draw_split(rng):
-    # few heads and a short query chunk against a long cache: the prefill
-    # kernel splits each 32-row tile over C = min(256 / tiles, blocks / 8, 8)
-    # workgroups (C = 2 .. 8 on 256 CUs)
+    # few heads and a short query chunk against a long cache, until one is drawn
+    # that the KV-cache kernel splits over ranges of the keys
+    while True:
+        c = _draw_cache(rng)
+        if plan_of(c["mode"], c["d"], c["bkv"], (c["b"], c["hq"], c["hkv"], c["nq"], c["nk"]), c["causal"])[1] == "split":
+            return c
+
+
+def _draw_cache(rng):
     mode = str(rng.choice(["fast", "fp8qk"]))
     d = int(rng.choice([64, 128]))
     bkv = int(rng.choice([64, 128]))
     hkv = int(rng.choice([1, 2]))
     hq = hkv * int(rng.choice([1, 2, 4]))
     b = int(rng.integers(1, 3))
-    nk = int(rng.integers(1100, 6000))
+    nk = int(rng.integers(3600, 9000))
     nq = int(rng.integers(1, 65))
     causal = bool(rng.integers(0, 2))
     order = str(rng.choice(["forward", "reverse"]))
@@ -84,6 +90,7 @@ def test_random_split_prefill(seed):
     c = _draw_split(np.random.default_rng(8000 + seed))
     label = f"random split seed={seed} {c}"
     log(label)
+    assert_splits(c["mode"], c["d"], c["bkv"], (c["b"], c["hq"], c["hkv"], c["nq"], c["nk"]), c["causal"])
     full = make_inputs(c["b"], c["hq"], c["hkv"], c["nk"], c["d"], fmt=FMT[c["mode"]],
                        delta=c["delta"], seed=8100 + seed)
     inp = last_queries(full, c["nq"])
