@@ -27,6 +27,7 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((__vector_size__(8 * sizeof(int)))) int i32x8;
 typedef __attribute__((__vector_size__(4 * sizeof(int)))) int i32x4;
 typedef __attribute__((__vector_size__(2 * sizeof(int)))) int i32x2;
+typedef __attribute__((__vector_size__(2 * sizeof(short)))) short s16x2;
 
 // Launch parameters (passed by value as the kernel argument block).
 struct Params {
@@ -130,6 +131,21 @@ __device__ inline UnitRange unit_range(const Params& p)
 __device__ inline int a_row_to_key(int m)
 {
     return ((m >> 2) & 1) * 16 + ((m >> 3) & 3) * 4 + (m & 3);
+}
+
+// Buffer over the K or V rows from `base` on.  Bytes past `left` read as 0,
+// whichever offset of a load (the lane's or the scalar one) crosses the end, and
+// with left = 0 a load costs no memory traffic.
+__device__ inline __amdgpu_buffer_rsrc_t row_buffer(const void* base, size_t left)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)(left < 0x40000000 ? left : 0x40000000),
+                                             0x00027000);
+}
+
+// Barrier for data exchanged through LDS; global loads in flight stay in flight.
+__device__ inline void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 // Value of the other 32-lane half of the wave.

@@ -88,25 +88,8 @@ __device__ inline T over_groups(T x, F f)
     return x;
 }
 
-typedef __attribute__((__vector_size__(2 * sizeof(short)))) short s16x2;
-typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
-typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2;
-
-// Buffer over the keys from `base` on; bytes past `left` read as 0.
-__device__ inline __amdgpu_buffer_rsrc_t key_buffer(const float* base, size_t left)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, (int)(left < 0x40000000 ? left : 0x40000000),
-                                             0x00027000);
-}
-
 template <int N>
 using vecf = __attribute__((__vector_size__(N * sizeof(float)))) float;
-
-// Barrier for data exchanged through LDS; global loads in flight stay in flight.
-__device__ inline void lds_barrier()
-{
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
 
 }  // namespace
 
@@ -189,8 +172,8 @@ __global__ void __launch_bounds__(64 * NW, 2) faithful_kernel(Params p)
         else
             return __builtin_bit_cast(VV, __builtin_amdgcn_raw_buffer_load_b32(vb, v_lane + 4 * VW * TR * (i % VT), so, 0));
     };
-    auto kbuf = [&](int t0) __attribute__((always_inline)) { return key_buffer(Kg + (size_t)t0 * D, (size_t)(Nk - t0) * ROW); };
-    auto vbuf = [&](int t0) __attribute__((always_inline)) { return key_buffer(Vg + (size_t)t0 * D, (size_t)(Nk - t0) * ROW); };
+    auto kbuf = [&](int t0) __attribute__((always_inline)) { return row_buffer(Kg + (size_t)t0 * D, (size_t)(Nk - t0) * ROW); };
+    auto vbuf = [&](int t0) __attribute__((always_inline)) { return row_buffer(Vg + (size_t)t0 * D, (size_t)(Nk - t0) * ROW); };
 
     V4 ka[PFK];
     VV va[PFV];

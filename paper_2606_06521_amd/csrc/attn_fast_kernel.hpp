@@ -56,8 +56,6 @@ namespace attn {
 
 namespace {
 
-typedef __attribute__((__vector_size__(2 * sizeof(short)))) short s16x2;
-
 // One 16-byte-per-lane direct load: lane i reads HBM bytes [base + voff, +16)
 // (base uniform, voff per lane) and writes LDS bytes [dst + 16 i, +16).
 // Issued as inline assembly so the compiler does not tie its completion to

@@ -62,25 +62,9 @@ namespace attn {
 
 namespace {
 
-typedef __attribute__((__vector_size__(2 * sizeof(short)))) short s16x2;
-
 __device__ inline i32x2 read_tr8(const uint8_t* p)
 {
     return __builtin_amdgcn_ds_read_tr8_b64_v2i32((__attribute__((address_space(3))) i32x2*)(p));
-}
-
-// Buffer over the bytes of a block's K or V rows; bytes past `left` read as 0
-// (and with left = 0 a load costs no memory traffic).
-__device__ inline __amdgpu_buffer_rsrc_t row_buffer(const uint8_t* base, size_t left)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(base), 0, (int)(left < 0x40000000 ? left : 0x40000000),
-                                             0x00027000);
-}
-
-// Barrier for data exchanged through LDS; global loads in flight stay in flight.
-__device__ inline void lds_barrier()
-{
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 // The MFMA shapes of a TR-row tile.  Lane (n, g): row n, group g of NG.

@@ -26,7 +26,6 @@
 #include <iterator>
 
 using namespace attn;
-typedef __attribute__((__vector_size__(2 * sizeof(short)))) short s16x2;
 
 // the FP32 modes' exp2 (FP64, rounded once)
 __global__ void k_exp2_f64(const float* x, int64_t n, float* out)
@@ -42,7 +41,7 @@ __global__ void __launch_bounds__(64) k_buffer_range(const uint8_t* base, int re
 {
     __shared__ __attribute__((aligned(1024))) i32x4 buf[64];
     const int lane = threadIdx.x;
-    const auto rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(base), 0, records, 0x00027000);
+    const auto rb = row_buffer(base, (size_t)records);
     if (form == 0) {
         out[lane] = __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rb, 16 * lane, soff, 0));
         return;
