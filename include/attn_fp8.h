@@ -58,8 +58,8 @@
  * Ownership and threading: every pointer is a device pointer owned by the
  * caller.  The library allocates no memory and keeps no state between calls;
  * it is reentrant.  The one scratch buffer a call can use, the workspace of a
- * KV-cache call whose 32-row tiles cannot fill the GPU (see attn_fp8_fwd_kv),
- * is passed in by the caller.  Work is enqueued on `stream` (a hipStream_t;
+ * KV-cache call whose tiles cannot fill the GPU (see attn_fp8_fwd_kv), is
+ * passed in by the caller.  Work is enqueued on `stream` (a hipStream_t;
  * NULL = the null stream) and runs asynchronously: a return of ATTN_OK means
  * "validated and launched"; synchronise on the stream before reading results.
  *
@@ -109,12 +109,13 @@ enum { ATTN_SCALE_DYNAMIC = 0x100 };
  *                  waves of a 32-row group take alternate KV blocks of the
  *                  visit and hand the running maximum to each other, so every
  *                  block still sees the running maximum of Algorithm 1.
- * Neither: ATTN_TILE_256, unless its units leave compute units idle and a
- * cost model of the two schedules' critical paths favours ATTN_TILE_128.
- * Both: ATTN_ERR_INVALID_ARG.  The two schedules
- * give identical E4M3 codes and counts; O and l differ only in FP32 rounding
- * (each 128-row group adds two partial sums at the end).  No effect in the
- * other modes or on short query chunks.
+ * Neither: ATTN_TILE_256, unless its units leave compute units idle: then the
+ * shortest, by a cost model, of the two and the KV-cache kernel (see
+ * attn_fp8_fwd_kv), for self-attention too.  Both: ATTN_ERR_INVALID_ARG.
+ * All three give identical E4M3 codes and counts; O and l differ only in FP32
+ * rounding (the 128-row schedule and the KV-cache kernel add partial sums at
+ * the end).  No effect in the other modes or on query chunks of fewer than
+ * 128 rows.
  */
 enum { ATTN_TILE_256 = 0x200, ATTN_TILE_128 = 0x400 };
 
@@ -218,30 +219,31 @@ int attn_fp8_p_underflow_count_descaled(const void* q, const void* k, const void
  *   counts [B][Hq][Nq][3] (count variant).
  *
  * With Nq = Nk these are attn_fp8_fwd_descaled / _p_underflow_count_descaled.
- * With Nq < Nk the fast modes run on a KV-cache kernel: the query rows of the
- * heads that share a KV head form tiles of 16 or 32 rows, and the eight waves
- * of a workgroup take a tile's KV blocks in rounds, handing the running
- * maximum on, so the P codes are those of the sequential visit; only the FP32
- * summation order of O and l differs.  (Long chunks, Nq >= 128 with Nk - Nq a
- * multiple of block_kv, run on the square problem's kernel instead.)  When
- * the tiles are fewer than the GPU's compute units, each tile can be split
- * over C = min(CUs / tiles, blocks / 8, 512 / rows) workgroups by ranges of its
- * keys; the call then enqueues three kernels (the range maxima, Algorithm 1
- * per range, a merge) and needs a device workspace:
+ * With Nq < 128 and Nq < Nk the fast modes run on a KV-cache kernel: the query
+ * rows of the heads that share a KV head form tiles of 16 or 32 rows, and the
+ * four or eight waves of a workgroup take a tile's KV blocks in rounds, handing
+ * the running maximum on, so the P codes are those of the sequential visit; only
+ * the FP32 summation order of O and l differs.  Longer chunks run on the square
+ * problem's kernels (ATTN_TILE_* above).  When the tiles are fewer than the
+ * GPU's compute units, each can be split over C = min(CUs / tiles, blocks / 8,
+ * 512 / rows) workgroups by ranges of its keys, where a cost model finds that
+ * shorter; the call then enqueues three kernels (the range maxima, Algorithm 1
+ * per range, a merge; a fourth clears the counts) and needs a device workspace:
  *   workspace        device memory of the caller, 256-byte aligned, or NULL.
  *                    The call uses it as scratch on `stream` (no contents are
  *                    read before the call writes them); calls that overlap in
  *                    time must not share one.  NULL runs the tiles without
  *                    that split (same codes and counts, fewer workgroups).
+ *                    Chunks of 128 rows or more that start at a block boundary
+ *                    make no use of it.
  *   workspace_bytes  its size; with a non-NULL workspace it should be what
  *                    attn_fp8_kv_workspace_bytes reports for the same shape on
  *                    the current device.  Less lowers C, down to
  *                    T * K * (32 d + 288) * 4 bytes for T = B Hq ceil(Nq / 32) < CUs
  *                    and K = min(CUs / T, blocks / 8, 8) > 1; below that
- *                    ATTN_ERR_INVALID_ARG.
+ *                    ATTN_ERR_INVALID_ARG, also for a call that would not split.
  * Nq > Nk returns ATTN_ERR_INVALID_ARG, Nk > 2^30 ATTN_ERR_UNSUPPORTED; other
- * arguments and return codes as
- * for the descaled entry points.
+ * arguments and return codes as for the descaled entry points.
  */
 int attn_fp8_fwd_kv(const void* q, const void* k, const void* v, float* out, float* lse,
                     int B, int Hq, int Hkv, int Nq, int Nk, int d, int causal,
@@ -262,7 +264,8 @@ int attn_fp8_p_underflow_count_kv(const void* q, const void* k, const void* v, i
  * tight serving loops, harnesses that forbid hipMalloc).  The KV-cache split
  * takes its scratch from a fixed device array inside the library instead:
  * 8 MiB per GPU, created when the library's code is loaded on that GPU and
- * held until the process ends.  The split never needs more than
+ * held until the process ends.  A call splits where attn_fp8_fwd_kv does with a
+ * workspace of the reported size.  The split never needs more than
  * CUs * (32 d + 288) * 4 + 512 bytes (4.5 MB on a 256-CU MI355X at d = 128);
  * a shape that would returns ATTN_ERR_SCRATCH, with nothing launched.  Every
  * call on one GPU shares that GPU's array: calls that overlap in time on one
@@ -278,14 +281,16 @@ int attn_fp8_fwd_kv_noalloc(const void* q, const void* k, const void* v, float* 
 
 /*
  * Workspace the KV-cache entry points can use for the shape (B, Hq, Hkv, Nq,
- * Nk, d, causal, block_kv, mode) on the current device: *bytes is set to 0
- * when the call would not split (square problems, long chunks, faithful
- * modes, tiles enough to fill the GPU), else to the larger of the range maxima
- * (units * C * rows floats) plus, from a 256-byte boundary, the partial sums
- * (units * C * (rows d + rows) floats) of the call's plan, and the least size
- * above.  Since units * C never exceeds the
- * CU count, this stays below CUs * (32 d + 288) * 4 + 512 bytes (4.5 MB on a
- * 256-CU MI355X at d = 128).  Queries the device's CU count; launches nothing.
+ * Nk, d, causal, block_kv, mode) on the current device: *bytes is set to 0 for
+ * square problems, chunks of 128 rows or more that start at a block boundary, the
+ * faithful modes, and where neither the call nor its least size above has
+ * anything to split; else to the larger of that least size and, for the plans of
+ * the forward and the count call, the range maxima (units * C * rows floats) plus,
+ * from a 256-byte boundary, the partial sums (units * C * (rows d + rows) floats).
+ * A call whose plan does not split leaves the workspace untouched.  Since units * C
+ * never exceeds the CU count, this stays below CUs * (32 d + 288) * 4 + 512 bytes
+ * (4.5 MB on a 256-CU MI355X at d = 128).  Queries the device's CU count; launches
+ * nothing.
  * Returns ATTN_OK, ATTN_ERR_INVALID_ARG (bad shape, NULL bytes),
  * ATTN_ERR_UNSUPPORTED, or ATTN_ERR_HIP if the device cannot be queried.
  */

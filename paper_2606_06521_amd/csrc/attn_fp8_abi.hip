@@ -23,7 +23,7 @@ __device__ __align__(256) uint8_t scratch[kScratchBytes];
 
 namespace {
 
-constexpr int kVersion = 620;   // 0.6.2: 128-row schedule of the fast kernel (ATTN_TILE_*)
+constexpr int kVersion = 630;   // 0.6.3: workspaces between the least and the reported size
 
 // Clears the diagnostic's output arrays on the caller's stream (a kernel, not
 // a memset node, so the call stays safe inside a captured graph).
@@ -282,7 +282,7 @@ void* scratch_on_device()
 
 // Shared validation and dispatch of the entry points.  ws: the caller's
 // workspace for the KV-cache split (nullptr: no split); a non-null ws must
-// hold at least the bytes attn_fp8_kv_workspace_bytes reports.
+// hold at least workspace_min bytes, and lowers the split below the reported size.
 int run(const void* q, const void* k, const void* v, float* out, float* lse,
         uint32_t* counts, bool count, int B, int Hq, int Hkv, int N, int Nk, int d, int causal,
         int block_kv, int order, float S, int mode_flags, int n_sink, float q_descale,
@@ -438,7 +438,8 @@ const char* attn_fp8_strerror(int status)
                "needs S = 2^k with 0 <= k <= 8; descales must be finite and positive; "
                "the block diagnostic needs all three arrays and 1 <= nbins <= 64; q, k, v and "
                "out must be 16-byte aligned, lse and counts 4-byte aligned, a workspace "
-               "256-byte aligned and at least attn_fp8_kv_workspace_bytes long)";
+               "256-byte aligned and not shorter than the least size of its shape (one of "
+               "attn_fp8_kv_workspace_bytes always does)";
     case ATTN_ERR_UNSUPPORTED:
         return "unsupported configuration (d and block_kv must be 64 or 128)";
     case ATTN_ERR_HIP:
