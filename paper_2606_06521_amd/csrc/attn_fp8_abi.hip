@@ -369,7 +369,7 @@ int attn_fp8_kv_workspace_bytes(int B, int Hq, int Hkv, int Nq, int Nk, int d, i
     Call cl;
     const int st = prepare(cl, false, B, Hq, Hkv, Nq, Nk, d, causal, block_kv, ATTN_ORDER_FORWARD,
                            256.0f, mode, 0, 1.0f, 1.0f, 1.0f);
-    if (st != ATTN_OK || cl.empty || !cl.fast)
+    if (st != ATTN_OK || cl.empty || !cl.fast || !attn::kv_may_split(shape(cl)))
         return st;
     int n_cu = 0;
     if (device_cus(n_cu) != ATTN_OK)
