@@ -90,7 +90,8 @@ inline void plan_bytes(KvPlan& pl, int d)
 //   total (5 x 8 heads x 32 queries x 95011 keys: 16-row tiles 300 us, 32-row
 //   ones 250).  Two workgroups that share a tile's columns go through its K at
 //   the same pace, so that each counts in full, 43 000 per CU (61 x 16384 keys on
-//   122 CUs: 124 us; split in four 104);
+//   122 CUs: 124 us; split in four 104), 49 000 where a head has several tiles (64 x
+//   32 queries x 4096 keys: 33 us on 256 CUs, one workgroup per tile 36);
 // - the counts take about a sixth more everywhere but on 32-row tiles with bf16
 //   scores at d = 128, blocks of 128, whose kernel spills (4096 x 4096, 4 heads: 51
 //   us, with counts 75, on 16-row tiles 76 and 81; the fast kernel 51 and 62; 2048 x
@@ -121,8 +122,9 @@ inline KvPlan kv_plan(const Shape& p, int n_cu, size_t ws_bytes)
         double mem = once / std::min(6.2e6, cu * active);
         if (!cached) {
             const double all = std::max(once, wgs * blocks * block_kv * row), again = all - once;
+            const double pairs = (pl.tiles > 1 ? 49e3 : 43e3) / 40e3 * cu;
             mem = std::max((once + again / 5) / 6.2e6,
-                           (pl.cols == 2 ? all / (43e3 / 40e3 * cu) : once / cu + again / 75e3) / active);
+                           (pl.cols == 2 ? all / pairs : once / cu + again / 75e3) / active);
         }
         return std::max(gens * ceil(blocks / pl.waves) * round + 4 * (gens - 1), mem);
     };
